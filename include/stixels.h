@@ -243,23 +243,28 @@ int stixels_get_frame_path(const stixels_handle *h);
 
 /* Wavefronts per column of the recurrence in stixels_compute (Sec. 4.3
  * assigns one thread block per column; here a column's rows are shared by
- * 1, 2 or 4 wave64s, interleaved by 64-row slot).  0 (the default) picks
- * automatically from the frame's column count and the device's compute
- * units; a request is capped by the rows: 4 needs more than 192 rows, 2
- * more than 64.  Results do not depend on it.  STIXELS_E_INVALID_ARG for
+ * 1, 2 or 4 wave64s, interleaved by 64-row slot).  0 (the default) is
+ * automatic: with no placement set either (stixels_set_po_placement), the
+ * staged path spreads a column over a workgroup of up to 16 wave64s, one of
+ * which runs the row-to-row chain; elsewhere the count is picked from the
+ * frame's column count and the device's compute units.  A request is capped by
+ * the rows: 4 needs more than 192 rows, 2 more than 64.  Results do not depend on it.  STIXELS_E_INVALID_ARG for
  * other values. */
 int stixels_set_waves(stixels_handle *h, int32_t waves);
 
-/* Waves per column that stixels_compute uses for a frame of this size under
- * the current setting (0 for a null handle or a size below the minimum). */
+/* Waves that share a column's rows for a frame of this size under the current
+ * setting (0 for a null handle or a size below the minimum); with the
+ * automatic setting, the count picked where a column is not spread over a
+ * workgroup. */
 int stixels_get_waves(const stixels_handle *h, int32_t height, int32_t width);
 
 /* Placement of a column's object prefix table (Sec. 4.2 keeps LUT_object in
  * global memory) for the recurrence of stixels_compute: 1 = read from
  * global memory (HBM and the caches); 2 = copied into the workgroup's LDS
  * when the column's table (its disparity rows x (height+1) floats) fits,
- * else global memory; 0 (the default) = as 2 for heights up to 512, as 1
- * above.  The LDS copy applies to one wave per column and max_disparity
+ * else global memory; 0 (the default) = global memory where a column is
+ * spread over a workgroup (stixels_set_waves 0), otherwise as 2 for heights
+ * up to 512, as 1 above.  The LDS copy applies to one wave per column and max_disparity
  * <= 128; other launches read global memory.  Results do not depend on it.
  * STIXELS_E_INVALID_ARG for other values. */
 int stixels_set_po_placement(stixels_handle *h, int32_t placement);

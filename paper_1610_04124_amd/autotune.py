@@ -174,11 +174,14 @@ def tune(batch, items, stream, replays: int = 9, cache_path: str | None = DEFAUL
 
 def tune_frame(handle, disp, out, stream, replays: int = 5, waves=WAVES,
                placements=(1, 2)) -> dict:
-    """Pick and apply waves per column and the object prefix table placement
-    (1 HBM, 2 LDS where it fits) of the per-frame path for frames of this
-    size; returns the timings."""
+    """Pick and apply the recurrence of the per-frame path for frames of this
+    size: the automatic setting (0, 0: a column spread over a workgroup), or
+    waves per column and the object prefix table placement (1 HBM, 2 LDS where
+    it fits); returns the timings."""
     H, W = disp.shape
-    timings = {}
+    handle.set_waves(0)
+    handle.set_po_placement(0)
+    timings = {(0, 0): _time(lambda: handle.compute(disp, out, stream), stream, replays)}
     for pl in placements:
         handle.set_po_placement(pl)
         for w in waves:
@@ -190,5 +193,5 @@ def tune_frame(handle, disp, out, stream, replays: int = 5, waves=WAVES,
     handle.set_waves(best[0])
     handle.set_po_placement(best[1])
     return {"waves": best[0], "po_placement": best[1], "ms": timings[best],
-            "tried": {f"w{w}/{'lds' if pl == 2 else 'hbm'}": round(v, 4)
+            "tried": {f"w{w}/{'lds' if pl == 2 else 'hbm'}" if w else "auto": round(v, 4)
                       for (w, pl), v in sorted(timings.items())}}

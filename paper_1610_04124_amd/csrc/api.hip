@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <new>
 #include <string>
 #include <vector>
@@ -112,12 +113,14 @@ void release(stixels_handle* h) {
     (void)hipFree(h->d_ground);
     (void)hipFree(h->d_object_t);
     (void)hipFree(h->d_object_df);
+    (void)hipFree(h->d_object_min);
     (void)hipFree(h->d_fg_hi);
     (void)hipFree(h->d_fg_lo);
     (void)hipFree(h->d_q);
     (void)hipFree(h->d_prefix);
     (void)hipFree(h->d_range);
     (void)hipFree(h->d_po);
+    (void)hipFree(h->d_edge);
     (void)hipFree(h->d_pose_ground);
     (void)hipFree(h->d_pose_hi);
     (void)hipFree(h->d_pose_lo);
@@ -180,6 +183,10 @@ int build_tables(stixels_handle* h) {
     h->object_df.resize((size_t)D * D);
     for (int f = 0; f < D; ++f)
         for (int d = 0; d < D; ++d) h->object_df[(size_t)d * D + f] = h->object_t[(size_t)f * D + d];
+    h->object_min.assign(D, std::numeric_limits<float>::infinity());
+    for (int f = 0; f < D; ++f)
+        for (int d = 0; d < D; ++d)
+            h->object_min[d] = std::min(h->object_min[d], h->object_t[(size_t)f * D + d]);
     // priors
     const double beta = to_grid(m.bic_cost, g);
     double fmaxp = 0.0, tmaxp = 0.0;
@@ -197,6 +204,9 @@ int build_tables(stixels_handle* h) {
     h->prior.c_grav = (float)to_grid(m.gravity_cost, g);
     h->prior.c_dive = (float)to_grid(m.diving_cost, g);
     h->prior.tau_ord = m.ordering_tol_px << k;     // in bins
+    h->prior.own_max = 0.0f;
+    for (int f = 0; f < D; ++f)
+        h->prior.own_max = std::max(h->prior.own_max, h->object_t[(size_t)f * D + f]);
     h->prior.mean_eps = (float)std::ldexp((double)D, -22);
     h->prior.exact = g >= 0 ? 1 : 0;
     if (g < 0) {
@@ -229,8 +239,20 @@ int build_tables(stixels_handle* h) {
 
 thread_local std::string g_create_error;
 
+// Bytes of the object prefix tables' entries 32 i for the widest frame.
+size_t edge_bytes(const stixels_handle* h) {
+    return (size_t)h->ncols_max * h->D * kEdgeFloats * sizeof(float);
+}
+
 // Path of stixels_compute: the request, or automatically the staged kernels.
 int frame_path_of(const stixels_handle* h) { return h->frame_path == 0 ? 1 : h->frame_path; }
+
+// Waves per column asked of the staged recurrence: those of a request, or 0
+// (the column spread over a workgroup, chain.h) when neither the waves nor the
+// placement of the object prefix table were set.
+int staged_waves(const stixels_handle* h, int waves) {
+    return (h->waves == 0 && h->po_placement == 0) ? 0 : waves;
+}
 
 }  // namespace
 
@@ -267,10 +289,13 @@ int stixels_create(const stixels_params* params, stixels_handle** out) {
         hipDeviceGetAttribute(&h->lds_per_block, hipDeviceAttributeMaxSharedMemoryPerBlock,
                               h->device) != hipSuccess)
         rc = fail(h, STIXELS_E_HIP, "cannot read the LDS size");
+    if (rc == STIXELS_OK && chain_setup(h->lds_per_block) != hipSuccess)
+        rc = fail(h, STIXELS_E_HIP, "cannot set the LDS size of the recurrence");
     if (rc == STIXELS_OK) rc = upload(h, &h->d_sky, h->sky);
     if (rc == STIXELS_OK) rc = upload(h, &h->d_ground, h->ground);
     if (rc == STIXELS_OK) rc = upload(h, &h->d_object_t, h->object_t);
     if (rc == STIXELS_OK) rc = upload(h, &h->d_object_df, h->object_df);
+    if (rc == STIXELS_OK) rc = upload(h, &h->d_object_min, h->object_min);
     if (rc == STIXELS_OK) rc = upload(h, &h->d_fg_hi, h->fg_hi);
     if (rc == STIXELS_OK) rc = upload(h, &h->d_fg_lo, h->fg_lo);
     if (rc == STIXELS_OK) rc = upload(h, &h->d_obj_k, h->obj_k);
@@ -279,12 +304,13 @@ int stixels_create(const stixels_params* params, stixels_handle** out) {
         // d_po holds the staged path's object prefix tables or, for the
         // fused path, its descriptor, task list and one scratch slot per
         // column
-        h->ws_bytes = std::max(nc * h->D * H1 * sizeof(float) + kTableGuardBytes,
+        h->ws_bytes = std::max(nc * h->D * po_row_floats(h->Hmax) * sizeof(float) + kTableGuardBytes,
                                persist::frame_fused_bytes(h->ncols_max, h->Hmax, h->D, h->ncols_max));
         bool ok = hipMalloc(reinterpret_cast<void**>(&h->d_q), nc * h->Hmax * sizeof(int16_t)) == hipSuccess &&
-                  hipMalloc(reinterpret_cast<void**>(&h->d_prefix), 4 * nc * H1 * sizeof(float)) == hipSuccess &&
+                  hipMalloc(reinterpret_cast<void**>(&h->d_prefix), 5 * nc * H1 * sizeof(float)) == hipSuccess &&
                   hipMalloc(reinterpret_cast<void**>(&h->d_range), 2 * nc * sizeof(int32_t)) == hipSuccess &&
                   hipMalloc(reinterpret_cast<void**>(&h->d_po), h->ws_bytes) == hipSuccess &&
+                  hipMalloc(reinterpret_cast<void**>(&h->d_edge), edge_bytes(h)) == hipSuccess &&
                   hipMalloc(reinterpret_cast<void**>(&h->d_pose_ground),
                             (size_t)h->Hmax * h->D * sizeof(float)) == hipSuccess &&
                   hipMalloc(reinterpret_cast<void**>(&h->d_pose_hi), (size_t)h->Hmax * sizeof(int32_t)) == hipSuccess &&
@@ -312,11 +338,12 @@ int stixels_destroy(stixels_handle* h) {
 int stixels_device_bytes(const stixels_handle* h, size_t* bytes) {
     if (!h || !bytes) return STIXELS_E_INVALID_ARG;
     size_t n = (h->sky.size() + h->ground.size() + h->object_t.size() + h->object_df.size() +
+                h->object_min.size() +
                 h->fg_hi.size() + h->fg_lo.size()) * 4;
     if (h->d_po) {
         const size_t nc = (size_t)h->ncols_max, H1 = (size_t)h->Hmax + 1;
-        n += nc * h->Hmax * sizeof(int16_t) + 4 * nc * H1 * sizeof(float) +
-             2 * nc * sizeof(int32_t) + h->ws_bytes +
+        n += nc * h->Hmax * sizeof(int16_t) + 5 * nc * H1 * sizeof(float) +
+             2 * nc * sizeof(int32_t) + h->ws_bytes + edge_bytes(h) +
              (size_t)h->Hmax * (h->D * sizeof(float) + 2 * sizeof(int32_t));
     }
     size_t b = 0;
@@ -397,14 +424,14 @@ int compute_frame(stixels_handle* h, const float* d_disparity, int32_t width, in
     }
     const int ncols = width / h->s;
     const int vtop = ground_top(m.horizon_row, height);
-    FrameWorkspace ws{h->d_q, h->d_prefix, h->d_range, h->d_po};
+    FrameWorkspace ws{h->d_q, h->d_prefix, h->d_range, h->d_po, h->d_edge};
     FrameOutput fo{out->counts, reinterpret_cast<uint32_t*>(out->records), out->total_cost,
                    out->overflow, out->capacity};
     hipError_t e = launch_reduce(m, d_disparity, width, height, ncols, ws.q, st);
     if (e == hipSuccess) e = launch_tables(m, ws, height, ncols, vtop, st);
     if (e == hipSuccess)
-        e = launch_dp(m, ws, height, ncols, vtop, waves, frame_po_lds(h->po_placement, height),
-                      h->lds_per_block, fo, st);
+        e = launch_dp(m, ws, height, ncols, vtop, staged_waves(h, waves),
+                      frame_po_lds(h->po_placement, height), h->lds_per_block, h->num_cu, fo, st);
     if (e != hipSuccess)
         return fail(h, STIXELS_E_HIP, std::string("kernel launch failed: ") + hipGetErrorString(e));
     h->last_W = width;
@@ -472,7 +499,7 @@ int stixels_debug_stage_times(stixels_handle* h, const float* d_disparity, int32
     const int vtop = ground_top(h->p.camera.horizon_row, height);
     const int waves = frame_waves(h->waves, height, ncols, h->num_cu);
     DeviceModel m = device_model(h);
-    FrameWorkspace ws{h->d_q, h->d_prefix, h->d_range, h->d_po};
+    FrameWorkspace ws{h->d_q, h->d_prefix, h->d_range, h->d_po, h->d_edge};
     FrameOutput fo{out->counts, reinterpret_cast<uint32_t*>(out->records), out->total_cost,
                    out->overflow, out->capacity};
     hipEvent_t ev[4] = {};
@@ -484,8 +511,8 @@ int stixels_debug_stage_times(stixels_handle* h, const float* d_disparity, int32
     if (e == hipSuccess) e = launch_tables(m, ws, height, ncols, vtop, st);
     if (e == hipSuccess) e = hipEventRecord(ev[2], st);
     if (e == hipSuccess)
-        e = launch_dp(m, ws, height, ncols, vtop, waves, frame_po_lds(h->po_placement, height),
-                      h->lds_per_block, fo, st);
+        e = launch_dp(m, ws, height, ncols, vtop, staged_waves(h, waves),
+                      frame_po_lds(h->po_placement, height), h->lds_per_block, h->num_cu, fo, st);
     if (e == hipSuccess) e = hipEventRecord(ev[3], st);
     if (e == hipSuccess) e = hipEventSynchronize(ev[3]);
     for (int i = 0; i < 3 && e == hipSuccess; ++i) e = hipEventElapsedTime(&host_ms[i], ev[i], ev[i + 1]);
@@ -644,6 +671,13 @@ int stixels_debug_stage(const stixels_handle* h, int32_t which, void* host_dst, 
     }
     if (bytes != n) return STIXELS_E_INVALID_ARG;
     if (hipStreamSynchronize(static_cast<hipStream_t>(stream)) != hipSuccess) return STIXELS_E_HIP;
+    if (which == STIXELS_STAGE_OBJECT_PREFIX) {
+        // H + 1 entries of each padded row
+        const hipError_t e = hipMemcpy2D(host_dst, (H + 1) * 4, h->d_po + 3,
+                                         (size_t)po_row_floats((int)H) * 4, (H + 1) * 4,
+                                         ncols * h->D, hipMemcpyDeviceToHost);
+        return e == hipSuccess ? STIXELS_OK : STIXELS_E_HIP;
+    }
     if (hipMemcpy(host_dst, src, n, hipMemcpyDeviceToHost) != hipSuccess) return STIXELS_E_HIP;
     return STIXELS_OK;
 }

@@ -15,6 +15,7 @@ struct DpArgs {
     const float* prefix;
     const int32_t* range;
     const float* po;
+    const float* edge;
     const int32_t* fg_hi;
     const int32_t* fg_lo;
     int32_t* counts;
@@ -71,7 +72,9 @@ __global__ __launch_bounds__(64 * W) void dp_kernel(DpArgs a) {
     in.PS = a.prefix + ((size_t)1 * a.ncols + col) * stride;
     in.PA = a.prefix + ((size_t)2 * a.ncols + col) * stride;
     in.PN2 = a.prefix + ((size_t)3 * a.ncols + col) * stride;
-    in.PO = a.po + (size_t)col * a.D * stride;
+    const int pstride = po_row_floats(a.H);
+    in.PO = a.po + (size_t)col * a.D * pstride + 3;
+    in.po_stride = pstride;
     in.fbase = a.range[2 * col];
     in.fmax = a.range[2 * col + 1];
     in.q = qs;
@@ -87,10 +90,10 @@ __global__ __launch_bounds__(64 * W) void dp_kernel(DpArgs a) {
     out.cap = a.cap;
     if constexpr (POL) {
         extern __shared__ float po_lds[];
-        const int n = (in.fmax - in.fbase + 1) * stride;   // uniform over the workgroup
-        if (n <= a.lds_floats) {
-            copy_to_lds<W>(po_lds, in.PO, n);
-            solve_column<S, NCH, W, true, false>(a.H, a.vtop, a.prior, in, out, lds, po_lds);
+        const int n = (in.fmax - in.fbase + 1) * pstride;  // uniform over the workgroup
+        if (n + 3 <= a.lds_floats) {
+            copy_to_lds<W>(po_lds, in.PO - 3, n);
+            solve_column<S, NCH, W, true, false>(a.H, a.vtop, a.prior, in, out, lds, po_lds + 3);
             return;
         }
     }

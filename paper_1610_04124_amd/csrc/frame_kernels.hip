@@ -12,6 +12,7 @@
 #include <map>
 #include <mutex>
 
+#include "chain.h"
 #include "dp_kernel.h"
 #include "kernel_table.h"
 #include "launch.h"
@@ -58,9 +59,11 @@ struct TablesArgs {
     float* prefix;
     int32_t* range;
     float* po;
+    float* edge;
     const float* sky;
     const float* ground;
     const float* object_t;
+    const float* object_min;
     // online object costs (instead of the offline LUT of Sec. 3.4): per mean
     // f, the Gaussian's constant part and 2 sigma^2 (FP64), the outlier cost
     const double* obj_k;
@@ -118,9 +121,13 @@ __global__ __launch_bounds__(512) void tables_kernel(TablesArgs a) {
     }
     const int stride = H + 1;
 
-    if (wave < 4) {
+    constexpr int U = kMaxHeight / 256;          // 256-row groups
+    const int nu = (H + 255) >> 8;
+    if (wave < 5) {
         // wave t scans small table t: ground, sky, 2q+1 and 2 over the valid
-        // pixels (four chains side by side rather than one after another)
+        // pixels and their smallest object costs (five chains side by side rather than one after another),
+        // lane l taking the rows 256 u + 4 l .. 256 u + 4 l + 3, so that a
+        // table of 440 rows is two loads and scans deep rather than seven
         const int t = __builtin_amdgcn_readfirstlane(wave);
         float* P = a.prefix + ((size_t)t * ncols + col) * stride;
         if (lane == 0) {
@@ -131,18 +138,32 @@ __global__ __launch_bounds__(512) void tables_kernel(TablesArgs a) {
             }
         }
         float carry = 0.0f;
-        for (int base = 0; base < H; base += 64) {
-            const int v = base + lane;
-            const int x = (v < H) ? (int)qs[v] : -1;
-            float e = 0.0f;
-            if (x >= 0) {
-                e = (t == 0) ? a.ground[(size_t)(H - 1 - v) * D + x]
-                  : (t == 1) ? a.sky[x]
-                  : (t == 2) ? (float)(2 * x + 1) : 2.0f;
+#pragma unroll 1
+        for (int u = 0; u < nu; ++u) {
+            float r[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int v = 256 * u + 4 * lane + i;
+                const int x = (v < H) ? (int)qs[v] : -1;
+                r[i] = 0.0f;
+                if (x >= 0) {
+                    r[i] = (t == 0) ? a.ground[(size_t)(H - 1 - v) * D + x]
+                         : (t == 1) ? a.sky[x]
+                         : (t == 2) ? (float)(2 * x + 1)
+                         : (t == 3) ? 2.0f : a.object_min[x];
+                }
             }
-            e = wave_inclusive_scan(e) + carry;
-            if (v < H) P[v + 1] = e;
-            carry = readlane_f(e, 63);
+            r[1] += r[0];
+            r[2] += r[1];
+            r[3] += r[2];
+            const float incl = wave_inclusive_scan(r[3]);
+            const float e = (incl - r[3]) + carry;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int v = 256 * u + 4 * lane + i;
+                if (v < H) P[v + 1] = r[i] + e;
+            }
+            carry = readlane_f(incl, 63) + carry;
         }
     }
 
@@ -156,12 +177,18 @@ __global__ __launch_bounds__(512) void tables_kernel(TablesArgs a) {
     // of a gather per 64 rows.  Every cost is on the grid, so the prefixes are
     // the same bits in any order of summation.
     __shared__ float ostg[8][256 + 4];
-    float* PO = a.po + (size_t)col * D * stride;
+    // Rows of the table are 16-byte aligned with entry i at float i + 3, so that
+    // a lane's four prefixes are one store; entries 32 i also go to a compact
+    // table of their own (one in 32 floats of a row, read alone, would fetch
+    // every line of it).
+    const int pstride = po_row_floats(H);
+    float* PO = a.po + (size_t)col * D * pstride;
+    float* edge = a.edge + (size_t)col * D * kEdgeFloats;
     const auto otr = make_rsrc(a.object_t, (uint32_t)(D * D) * 4u);
-    const auto pow_ = make_rsrc(PO, (uint32_t)(fmax - fmin + 1) * (uint32_t)stride * 4u);
-    constexpr int U = kMaxHeight / 256;          // 256-row groups
+    const auto pow_ = make_rsrc(PO, (uint32_t)(fmax - fmin + 1) * (uint32_t)pstride * 4u);
+    const auto edr = make_rsrc(edge, (uint32_t)(fmax - fmin + 1) * (uint32_t)kEdgeFloats * 4u);
     constexpr int NC = 4;                        // 64-bin chunks of a cost row (<= 256 bins)
-    const int nu = (H + 255) >> 8, nch = (D + 63) >> 6;
+    const int nch = (D + 63) >> 6;
     float* const stg = ostg[wave];
     if (lane == 0) stg[D] = 0.0f;
     int qi[U][4];                                // stage index of each row's cost
@@ -197,8 +224,12 @@ __global__ __launch_bounds__(512) void tables_kernel(TablesArgs a) {
             if (64 * c + lane < D) stg[64 * c + lane] = onext[c];
         }
         if (f + 8 <= f1) load_row(f + 8);
-        const uint32_t rowoff = (uint32_t)(f - f0) * (uint32_t)stride * 4u;
-        if (lane == 0) buf_store_b(pow_, 0.0f, 0u, rowoff);
+        const uint32_t rowoff = (uint32_t)(f - f0) * (uint32_t)pstride * 4u;
+        const uint32_t edgeoff = (uint32_t)(f - f0) * (uint32_t)kEdgeFloats * 4u;
+        if (lane == 0) {
+            buf_store_b(pow_, 0.0f, 12u, rowoff);
+            buf_store_b(edr, 0.0f, 0u, edgeoff);
+        }
         float carry = 0.0f;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -208,15 +239,45 @@ __global__ __launch_bounds__(512) void tables_kernel(TablesArgs a) {
             const float a1 = o0 + o1, a2 = a1 + o2, a3 = a2 + o3;
             const float incl = wave_inclusive_scan(a3);
             const float e = (incl - a3) + carry;
-            const float r[4] = {e + o0, e + a1, e + a2, e + a3};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int v = 256 * u + 4 * lane + i;
-                if (v < H) buf_store_b(pow_, r[i], (uint32_t)(v + 1) * 4u, rowoff);
-            }
+            const int v = 256 * u + 4 * lane;    // the lane's first row
+            if (v < H)
+                buf_store_b4(pow_, e + o0, e + a1, e + a2, e + a3, (uint32_t)(v + 4) * 4u, rowoff);
+            if ((lane & 7) == 7 && v + 4 <= H)
+                buf_store_b(edr, e + a3, (uint32_t)(v + 4) / 32u * 4u, edgeoff);
             carry = readlane_f(incl, 63) + carry;
         }
     }
+}
+
+// ------------------------------------------------------------------ dp
+// The recurrence of one frame, a workgroup of chain_waves(H) waves per column
+// (chain.h).
+__global__ __launch_bounds__(64 * kChainWaves)
+__attribute__((amdgpu_waves_per_eu(4))) void chain_kernel(DpArgs a) {
+    extern __shared__ __align__(16) char chain_mem[];
+    const int col = blockIdx.x;
+    const int stride = a.H + 1;
+    ColumnIn in{};
+    in.PG = a.prefix + ((size_t)0 * a.ncols + col) * stride;
+    in.PS = a.prefix + ((size_t)1 * a.ncols + col) * stride;
+    in.PA = a.prefix + ((size_t)2 * a.ncols + col) * stride;
+    in.PN2 = a.prefix + ((size_t)3 * a.ncols + col) * stride;
+    const int pstride = po_row_floats(a.H);
+    in.PO = a.po + (size_t)col * a.D * pstride + 3;
+    in.po_stride = pstride;
+    in.PO_edge = a.edge + (size_t)col * a.D * kEdgeFloats;
+    in.fbase = __builtin_amdgcn_readfirstlane(a.range[2 * col]);
+    in.fmax = __builtin_amdgcn_readfirstlane(a.range[2 * col + 1]);
+    in.PM = a.prefix + ((size_t)4 * a.ncols + col) * stride;
+    in.fg_hi = a.fg_hi;
+    in.fg_lo = a.fg_lo;
+    ColumnOut out;
+    out.count = a.counts + col;
+    out.rec = a.records + (size_t)col * a.cap * 3;
+    out.total = a.total + col;
+    out.overflow = a.overflow + col;
+    out.cap = a.cap;
+    solve_chain(a.H, a.vtop, a.prior, in, out, chain_mem);
 }
 
 // ------------------------------------------------------------------ self-test
@@ -277,9 +338,11 @@ hipError_t launch_tables(const DeviceModel& m, const FrameWorkspace& ws, int H, 
     a.prefix = ws.prefix;
     a.range = ws.range;
     a.po = ws.po;
+    a.edge = ws.edge;
     a.sky = m.sky;
     a.ground = m.ground;
     a.object_t = m.object_t;
+    a.object_min = m.object_min;
     a.obj_k = m.obj_k;
     a.c_out = m.c_out;
     a.online = m.object_online;
@@ -335,8 +398,14 @@ bool frame_po_lds(int placement, int H) {
     return placement == 2 || (placement == 0 && kernel_slots(H) <= 8);
 }
 
+hipError_t chain_setup(int lds_per_block) {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&chain_kernel),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, lds_per_block);
+}
+
 hipError_t launch_dp(const DeviceModel& m, const FrameWorkspace& ws, int H, int ncols, int vtop,
-                     int waves, bool po_lds, int lds_per_block, const FrameOutput& out,
+                     int waves, bool po_lds, int lds_per_block, int num_cu,
+                     const FrameOutput& out,
                      hipStream_t st) {
     DpArgs a;
     a.q = ws.q;
@@ -344,6 +413,7 @@ hipError_t launch_dp(const DeviceModel& m, const FrameWorkspace& ws, int H, int 
     a.prefix = ws.prefix;
     a.range = ws.range;
     a.po = ws.po;
+    a.edge = ws.edge;
     a.fg_hi = m.fg_hi;
     a.fg_lo = m.fg_lo;
     a.counts = out.counts;
@@ -357,6 +427,11 @@ hipError_t launch_dp(const DeviceModel& m, const FrameWorkspace& ws, int H, int 
     a.vtop = vtop;
     a.lds_floats = 0;
     a.prior = m.prior;
+    if (waves == 0) {
+        void* args[] = {&a};
+        return hipLaunchKernel(reinterpret_cast<const void*>(&chain_kernel), dim3(ncols),
+                               dim3(64 * chain_waves(H, ncols <= num_cu ? 16 : 8)), args, chain_lds_bytes(H), st);
+    }
     const int slots = kernel_slots(H), nch = kernel_chunks(m.D);
     // the LDS copy exists for one wave per column and d_range <= 128 only:
     // with both recurrences in one kernel the other variants run out of

@@ -23,7 +23,7 @@ struct stixels_handle {
     size_t ws_bytes = 0;    // bytes of d_po (the fused path's whole workspace)
     stixels_batch* auto_batch = nullptr;   // batch object behind stixels_compute_batch
     // host copies of the rounded tables
-    std::vector<float> sky, ground, object_t, object_df;
+    std::vector<float> sky, ground, object_t, object_df, object_min;
     std::vector<int32_t> fg_hi, fg_lo;
     std::vector<double> obj_k;   // per mean: Gaussian constant part, 2 sigma^2
     double c_out = 0.0;
@@ -33,6 +33,7 @@ struct stixels_handle {
     float* d_ground = nullptr;
     float* d_object_t = nullptr;
     float* d_object_df = nullptr;
+    float* d_object_min = nullptr;
     int32_t* d_fg_hi = nullptr;
     int32_t* d_fg_lo = nullptr;
     // per-frame workspace
@@ -40,6 +41,7 @@ struct stixels_handle {
     float* d_prefix = nullptr;
     int32_t* d_range = nullptr;
     float* d_po = nullptr;
+    float* d_edge = nullptr;
     // the ground table and thresholds of the last frame with its own pose
     float* d_pose_ground = nullptr;    // [Hmax][D]
     int32_t* d_pose_hi = nullptr;      // [Hmax]
@@ -52,7 +54,8 @@ struct stixels_handle {
 
 // Device view of a handle's resident tables and priors.
 inline stx::DeviceModel device_model(const stixels_handle* h) {
-    stx::DeviceModel m{h->d_sky, h->d_ground, h->d_object_t, h->d_object_df, h->d_fg_hi,
+    stx::DeviceModel m{h->d_sky, h->d_ground, h->d_object_t, h->d_object_df,
+                       h->d_object_min, h->d_fg_hi,
                        h->d_fg_lo, h->D, h->Hmax, h->p.reduce_mode,
                        h->p.subpixel_log2, h->s,
                        h->p.camera.horizon_row, h->prior};

@@ -2,11 +2,15 @@
 //
 // Layout in HBM (per frame, per reduced column i of height h):
 //   q      int16 [ncols][h]            reduced disparities, bottom-up, -1 invalid
-//   prefix float [4][ncols][h+1]       PG (ground), PS (sky), PA = 2*sum(q)+count,
-//                                      PN2 = 2*count; entry v+1 covers rows 0..v
+//   prefix float [5][ncols][h+1]       PG (ground), PS (sky), PA = 2*sum(q)+count,
+//                                      PN2 = 2*count; entry v+1 covers rows 0..v;
+//                                      a fifth, PM, sums each pixel's smallest
+//                                      object cost over all means
 //   range  int32 [ncols][2]            smallest / largest valid q of the column
-//   PO     float [ncols][D][h+1]       object prefix table, row f-fmin holds
-//                                      sum over rows of O[q_v][f]
+//   PO     float [ncols][D][po_row_floats(h)]  object prefix table, row f-fmin
+//                                      holds sums over rows of O[q_v][f]; entry
+//                                      i sits at float i + 3 of its row
+//   edge   float [ncols][D][33]        entries 32 i of the rows of PO
 // Every cost value is a multiple of 2^-g and every partial sum stays below
 // 2^(24-g) in magnitude (checked when a handle is created), so FP32 adds,
 // subtractions and minima are exact and their order does not matter.
@@ -30,6 +34,12 @@ constexpr uint32_t kBufferWord3 = 0x00020000u;  // raw buffer resource, gfx9 fam
 // floats beyond the column's last table row (their values are never used),
 // and this keeps those reads inside the allocation.
 constexpr size_t kTableGuardBytes = 64 * 1024;
+
+// Floats of a row of the per-frame object prefix table (h + 1 entries, the
+// first at float 3: entries 4l+1 .. 4l+4 form one aligned 16-byte store) and
+// of a row of its entries 32 i.
+__host__ __device__ constexpr int po_row_floats(int h) { return ((h + 10) / 4) * 4; }
+constexpr int kEdgeFloats = kMaxHeight / 32 + 1;
 
 // Instantiated slot counts of the recurrence kernels (64-row slots per lane);
 // a column runs on the smallest one that covers its height.
@@ -72,6 +82,7 @@ struct Prior {
     float c_ord, c_grav, c_dive;
     int tau_ord;
     float mean_eps;       // bias of the rounded-mean division, d_range * 2^-22
+    float own_max;        // largest object cost of a pixel at a mean equal to it
     int exact;            // 1: every cost is on the 2^-g grid (FP32 sums are exact)
 };
 

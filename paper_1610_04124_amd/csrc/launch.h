@@ -14,6 +14,7 @@ struct DeviceModel {
     const float* ground;    // [max_height][D], top-down image rows
     const float* object_t;  // [D][D], row f: cost of pixel disparity d for mean f
     const float* object_df; // [D][D], row d: cost of pixel disparity d for every mean f
+    const float* object_min;// [D], smallest object cost of a pixel disparity over all means
     const int32_t* fg_hi;   // [max_height], top-down image rows
     const int32_t* fg_lo;
     int D;
@@ -34,9 +35,10 @@ struct DeviceModel {
 // Per-frame workspace views.
 struct FrameWorkspace {
     int16_t* q;        // [ncols][H]
-    float* prefix;     // [4][ncols][H+1]
+    float* prefix;     // [5][ncols][H+1]
     int32_t* range;    // [ncols][2]
-    float* po;         // [ncols][D][H+1]
+    float* po;         // [ncols][D][po_row_floats(H)]
+    float* edge;       // [ncols][D][33]: entries 32 i of the rows of po
 };
 
 struct FrameOutput {
@@ -57,9 +59,15 @@ int frame_waves(int requested, int H, int ncols, int num_cu);
 // Whether the per-frame recurrence tries the LDS copy of the object prefix
 // table: placement 0 automatic, 1 never (HBM), 2 wherever it fits.
 bool frame_po_lds(int placement, int H);
-// lds_per_block: the device's LDS limit per workgroup (bytes).
+// Lets the current device's launches of the chain recurrence use up to
+// lds_per_block bytes of LDS (once per device; repeating it is harmless).
+hipError_t chain_setup(int lds_per_block);
+// waves: wave64s per column (1, 2 or 4), or 0: the column spread over a
+// workgroup (chain.h).  lds_per_block: the device's LDS limit per workgroup
+// (bytes).
 hipError_t launch_dp(const DeviceModel& m, const FrameWorkspace& ws, int H, int ncols, int vtop,
-                     int waves, bool po_lds, int lds_per_block, const FrameOutput& out,
+                     int waves, bool po_lds, int lds_per_block, int num_cu,
+                     const FrameOutput& out,
                      hipStream_t st);
 hipError_t run_selftest_mean(int D, int max_height, int64_t* mismatches);
 
