@@ -217,13 +217,14 @@ int stixels_compute_pose(stixels_handle *h, const float *d_disparity, int32_t wi
                          int32_t height, const stixels_pose *pose, void *stream,
                          const stixels_output *out);
 
-/* How stixels_compute runs a frame: 1 = three staged kernels (reduction and
- * transpose, prefix tables into the handle's workspace, recurrence and
- * backtracking: Sec. 4.1, 4.2, 4.3-4.4 as separate steps, as in the paper);
- * 2 = one launch of the persistent fused kernel of the batch API over the
+/* How stixels_compute runs a frame: 1 = the staged path, which leaves the
+ * intermediates of Sec. 4.1 and 4.2 in the handle's workspace: three kernels
+ * (reduction and transpose, prefix tables, recurrence and backtracking) when
+ * waves or placement are set or the object costs are online, otherwise one
+ * launch that takes each column through all of them; 2 = one launch over the
  * frame's columns (each column reduced, tabulated, solved and backtracked
- * inside one workgroup, its tables in a scratch slot of the handle's
- * workspace); 0 (the default) = automatic (currently 1).  Results do not
+ * inside one workgroup, its object prefix table in the handle's workspace);
+ * 0 (the default) = automatic (currently 1).  Results do not
  * depend on it.  The intermediates of stixels_debug_stage exist only after a
  * staged call.  STIXELS_E_INVALID_ARG for other values. */
 int stixels_set_frame_path(stixels_handle *h, int32_t path);
@@ -337,9 +338,11 @@ int stixels_batch_replay(stixels_batch *b, void *stream);
 int stixels_batch_set_workgroups(stixels_batch *b, int32_t workgroups);
 
 /* Wavefronts per column of later calls (as in stixels_set_waves: 1, 2 or
- * 4, capped by the batch's row slots; 0 = 1); used by the autotuner.
- * Results do not depend on it.  Takes effect at the next compute or
- * capture. */
+ * 4, capped by the batch's row slots); 0 (the default) = automatic: launches
+ * of frames taller than 512 rows, and short launches of others, spread each
+ * column over a workgroup of up to 16 wave64s, the rest use one wave per
+ * column.  Used by the autotuner.  Results do not depend on it.  Takes effect
+ * at the next compute or capture. */
 int stixels_batch_set_waves(stixels_batch *b, int32_t waves);
 
 /* Waves per column of the last compute or capture (0 before the first). */

@@ -98,10 +98,12 @@ WAVES = (1, 2, 4)
 
 
 def tune(batch, items, stream, replays: int = 9, cache_path: str | None = DEFAULT_CACHE,
-         force: bool = False, waves=WAVES) -> dict:
+         force: bool = False, waves=(0,) + WAVES) -> dict:
     """Pick and apply waves per column and the workgroup count for `items`
     on `batch`; returns the record (also cached).  Leaves the batch captured
-    with the chosen configuration."""
+    with the chosen configuration.  waves 0 stands for the automatic choice
+    where that spreads a column over a workgroup (elsewhere it equals one of
+    the others and is not timed)."""
     key = device_key() + "||" + signature(items)
     cache = _load(cache_path) if cache_path else {}
     if not force and key in cache and "columns" in cache[key]:
@@ -122,7 +124,7 @@ def tune(batch, items, stream, replays: int = 9, cache_path: str | None = DEFAUL
         batch.set_columns(c)
         batch.set_workgroups(0)
         batch.capture(items, stream)
-        if batch.waves() != w or batch.columns() != c:
+        if batch.columns() != c or (batch.waves() != w if w else batch.waves() <= max(WAVES)):
             continue                               # not available for these rows
         gmax, nt = batch.info()
         for g in candidates(gmax, nt):

@@ -10,6 +10,7 @@
 #include <string>
 #include <vector>
 
+#include "chain_frame.h"
 #include "handle.h"
 #include "job_desc.h"
 #include "launch.h"
@@ -289,7 +290,8 @@ int stixels_create(const stixels_params* params, stixels_handle** out) {
         hipDeviceGetAttribute(&h->lds_per_block, hipDeviceAttributeMaxSharedMemoryPerBlock,
                               h->device) != hipSuccess)
         rc = fail(h, STIXELS_E_HIP, "cannot read the LDS size");
-    if (rc == STIXELS_OK && chain_setup(h->lds_per_block) != hipSuccess)
+    if (rc == STIXELS_OK && (chain_setup(h->lds_per_block) != hipSuccess ||
+                             persist::chain_frame_setup(h->lds_per_block) != hipSuccess))
         rc = fail(h, STIXELS_E_HIP, "cannot set the LDS size of the recurrence");
     if (rc == STIXELS_OK) rc = upload(h, &h->d_sky, h->sky);
     if (rc == STIXELS_OK) rc = upload(h, &h->d_ground, h->ground);
@@ -406,20 +408,27 @@ int compute_frame(stixels_handle* h, const float* d_disparity, int32_t width, in
         m.horizon_row = pose->horizon_row;
     }
     const int waves = frame_waves(h->waves, height, width / h->s, h->num_cu);
-    if (path == 2) {
-        int grid = 0;
+    // Neither waves nor placement set (and costs on the grid): one launch with
+    // a workgroup per column, on the staged path leaving the intermediates
+    // where its kernels leave them
+    const bool chain = h->prior.exact && staged_waves(h, waves) == 0;
+    if (path == 2 || (chain && h->object_lut == 0)) {
         persist::JobDesc job = persist::make_job_desc(h, d_disparity, width, height, *out);
         job.ground = m.ground;
         job.fg_hi = m.fg_hi;
         job.fg_lo = m.fg_lo;
         job.vtop = ground_top(m.horizon_row, height);
-        const hipError_t e = persist::launch_frame_fused(job, h->d_po, h->ws_bytes, waves,
-                                                         h->num_cu, st, &grid);
+        int grid = 0;
+        const persist::ChainExports ex = path == 1
+            ? persist::ChainExports{h->d_q, h->d_range, h->d_prefix} : persist::ChainExports{};
+        const hipError_t e = chain
+            ? persist::launch_chain_frame(job, h->d_po, ex, h->num_cu, st)
+            : persist::launch_frame_fused(job, h->d_po, h->ws_bytes, waves, h->num_cu, st, &grid);
         if (e != hipSuccess)
             return fail(h, STIXELS_E_HIP, std::string("kernel launch failed: ") + hipGetErrorString(e));
         h->last_W = width;
         h->last_H = height;
-        h->last_path = 2;
+        h->last_path = path;
         return STIXELS_OK;
     }
     const int ncols = width / h->s;

@@ -7,6 +7,7 @@
 #include <string>
 #include <vector>
 
+#include "chain_frame.h"
 #include "job_desc.h"
 #include "kernel_table.h"
 #include "launch.h"
@@ -73,7 +74,7 @@ struct stixels_batch {
     bool staged_pending = false;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    int waves = 1;          // requested waves per column
+    int waves = 0;          // requested waves per column (0: automatic)
     int columns = 1;        // requested columns per wave (2: the pair kernel where it exists)
     int last_columns = 0;
     int last_grid = 0, last_tasks = 0, last_waves = 0;
@@ -96,6 +97,20 @@ int batch_waves_for(const stixels_batch* b, int slots) {
     return std::min(std::max(b->waves, 1), cap);
 }
 
+// Whether an automatic launch spreads each column over a workgroup
+// (chain_frame.hip) rather than giving it a persistent wave.  Above 512 rows
+// always: the wave's recurrence then runs a loop over slots that it cannot
+// unroll (8 frames 2048x880, 3,272 columns: 1,224 us against 4,992, or 3,172
+// with two waves a column; 32 frames 1280x720, 8,192 columns: 1,952 against
+// 3,766).  Below, while the launch is short: a wave per column takes as long
+// as its chain of steps however few the columns are, but costs less once every
+// SIMD has its waves.  Measured crossings, columns per compute unit: 640x120 8,
+// 640x240 10, 832x320 9, 1024x440 24, 1152x505 19 (3 frames 1024x440: 150 us
+// against 261; 20: 564 against 587; 64: 1,900 against 1,380).
+bool chain_pays(const stixels_batch* b, int hmax, int ntasks) {
+    return hmax > 512 || (long long)ntasks <= (long long)b->num_cu * (hmax > 384 ? 18 : 9);
+}
+
 int occupancy_grid(stixels_batch* b, int slots, int nch, int waves, int* grid,
                    bool links = false) {
     int per_cu = 0;
@@ -110,7 +125,8 @@ int occupancy_grid(stixels_batch* b, int slots, int nch, int waves, int* grid,
 // Validate the jobs and fill the pinned staging buffers: descriptors and the
 // task list in decreasing-height order.
 int stage(stixels_batch* b, const stixels_job* jobs, int32_t n, int* slots, int* nch,
-          int* ntasks, long long* stride, int* hmax_out, bool want_pairs, bool* pairs_out) {
+          int* ntasks, long long* stride, int* hmax_out, int* dmax_out, bool want_pairs,
+          bool* pairs_out) {
     if (!jobs || n < 1 || n > b->cfg.max_jobs)
         return bfail(b, STIXELS_E_INVALID_ARG, "job count outside [1, max_jobs]");
     int hmax = 0, dmax = 0;
@@ -188,6 +204,7 @@ int stage(stixels_batch* b, const stixels_job* jobs, int32_t n, int* slots, int*
     *stride = pairs ? 2LL * (8 + dmax) * (hmax + 1) : slot_floats(hmax, dmax);
     *pairs_out = pairs;
     *hmax_out = hmax;
+    *dmax_out = dmax;
     return STIXELS_OK;
 }
 
@@ -229,6 +246,57 @@ int upload(stixels_batch* b, JobDesc* dj, int2* dt, PoseItem* dp, int n, int nta
         return bfail(b, STIXELS_E_HIP, "event record failed");
     b->staged_pending = true;
     return STIXELS_OK;
+}
+
+// How the staged jobs run: the kernel, its grid and scratch.
+struct Plan {
+    int slots = 0, nch = 0, ntasks = 0, hmax = 0, waves = 0, grid = 0;
+    long long stride = 0;
+    bool pairs = false, chain = false;
+};
+
+// Stages the jobs and picks their launch.
+int plan(stixels_batch* b, const stixels_job* jobs, int32_t n, Plan* p) {
+    int dmax = 0;
+    int rc = stage(b, jobs, n, &p->slots, &p->nch, &p->ntasks, &p->stride, &p->hmax, &dmax,
+                   b->columns == 2, &p->pairs);
+    if (rc != STIXELS_OK) return rc;
+    p->chain = b->waves == 0 && !p->pairs && !b->links && chain_pays(b, p->hmax, p->ntasks);
+    if (p->chain) {
+        p->waves = chain_batch_waves(p->hmax, p->ntasks, b->num_cu);
+        p->stride = (long long)chain_table_floats(p->hmax, dmax);
+        long long g = std::min<long long>((long long)chain_batch_per_cu(p->waves) * b->num_cu,
+                                          (long long)(b->scratch_floats / (size_t)p->stride));
+        if (b->cfg.workgroups > 0) g = std::min<long long>(g, b->cfg.workgroups);
+        p->grid = (int)std::min<long long>(g, p->ntasks);
+        if (p->grid >= 1) return STIXELS_OK;
+        p->chain = false;   // less scratch than one table: the persistent kernel's rules decide
+        p->stride = slot_floats(p->hmax, dmax);
+    }
+    p->waves = (p->pairs || b->links) ? 1 : batch_waves_for(b, p->slots);
+    return choose_grid(b, p->slots, p->nch, p->waves, p->pairs, p->stride, p->ntasks, &p->grid);
+}
+
+hipError_t launch(stixels_batch* b, const Plan& p, const JobDesc* jobs, const int2* tasks,
+                  unsigned int* counter, const PoseItem* poses, hipStream_t st) {
+    const hipError_t e = launch_pose_tables(poses, b->npose, b->pose_hmax, st);
+    if (e != hipSuccess) return e;
+    if (p.chain) {
+        hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, st, counter);
+        return launch_chain_batch(jobs, tasks, p.ntasks, counter, b->d_scratch, p.stride, p.hmax,
+                                  p.grid, p.waves, st);
+    }
+    return p.pairs ? launch_pair_batch(p.slots, p.nch, p.grid, st, jobs, tasks, p.ntasks, counter,
+                                       b->d_scratch, p.stride, p.hmax)
+                   : launch_batch(p.slots, p.nch, p.waves, b->links, p.grid, st, jobs, tasks,
+                                  p.ntasks, counter, b->d_scratch, p.stride, p.hmax);
+}
+
+void remember(stixels_batch* b, const Plan& p) {
+    b->last_grid = p.grid;
+    b->last_tasks = p.ntasks;
+    b->last_waves = p.waves;
+    b->last_columns = p.pairs ? 2 : 1;
 }
 
 void destroy_graph(stixels_batch* b) {
@@ -342,28 +410,16 @@ int stixels_batch_destroy(stixels_batch* b) {
 
 int stixels_batch_compute(stixels_batch* b, const stixels_job* jobs, int32_t n, void* stream) {
     if (!b) return STIXELS_E_INVALID_ARG;
-    int slots = 0, nch = 0, ntasks = 0, grid = 0, hmax = 0;
-    long long stride = 0;
-    bool pairs = false;
-    int rc = stage(b, jobs, n, &slots, &nch, &ntasks, &stride, &hmax, b->columns == 2, &pairs);
-    const int waves = (pairs || b->links) ? 1 : batch_waves_for(b, slots);
-    if (rc == STIXELS_OK) rc = choose_grid(b, slots, nch, waves, pairs, stride, ntasks, &grid);
+    Plan p;
+    int rc = plan(b, jobs, n, &p);
     if (rc != STIXELS_OK) return rc;
     const hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = upload(b, b->d_jobs, b->d_tasks, b->d_pose_items, n, ntasks, st);
+    rc = upload(b, b->d_jobs, b->d_tasks, b->d_pose_items, n, p.ntasks, st);
     if (rc != STIXELS_OK) return rc;
-    hipError_t e = launch_pose_tables(b->d_pose_items, b->npose, b->pose_hmax, st);
-    if (e == hipSuccess)
-        e = pairs ? launch_pair_batch(slots, nch, grid, st, b->d_jobs, b->d_tasks, ntasks,
-                                  b->d_counter, b->d_scratch, stride, hmax)
-              : launch_batch(slots, nch, waves, b->links, grid, st, b->d_jobs, b->d_tasks, ntasks,
-                             b->d_counter, b->d_scratch, stride, hmax);
+    const hipError_t e = launch(b, p, b->d_jobs, b->d_tasks, b->d_counter, b->d_pose_items, st);
     if (e != hipSuccess)
         return bfail(b, STIXELS_E_HIP, std::string("batch launch failed: ") + hipGetErrorString(e));
-    b->last_grid = grid;
-    b->last_tasks = ntasks;
-    b->last_waves = waves;
-    b->last_columns = pairs ? 2 : 1;
+    remember(b, p);
     return STIXELS_OK;
 }
 
@@ -371,16 +427,12 @@ int stixels_batch_capture(stixels_batch* b, const stixels_job* jobs, int32_t n, 
     if (!b) return STIXELS_E_INVALID_ARG;
     if (!stream)
         return bfail(b, STIXELS_E_INVALID_ARG, "the null stream cannot be captured; pass a created stream");
-    int slots = 0, nch = 0, ntasks = 0, grid = 0, hmax = 0;
-    long long stride = 0;
-    bool pairs = false;
-    int rc = stage(b, jobs, n, &slots, &nch, &ntasks, &stride, &hmax, b->columns == 2, &pairs);
-    const int waves = (pairs || b->links) ? 1 : batch_waves_for(b, slots);
-    if (rc == STIXELS_OK) rc = choose_grid(b, slots, nch, waves, pairs, stride, ntasks, &grid);
+    Plan p;
+    int rc = plan(b, jobs, n, &p);
     if (rc != STIXELS_OK) return rc;
     const hipStream_t st = static_cast<hipStream_t>(stream);
     // the graph reads its own descriptor copy, uploaded once here
-    rc = upload(b, b->d_jobs_g, b->d_tasks_g, b->d_pose_items_g, n, ntasks, st);
+    rc = upload(b, b->d_jobs_g, b->d_tasks_g, b->d_pose_items_g, n, p.ntasks, st);
     if (rc != STIXELS_OK) return rc;
     if (hipStreamSynchronize(st) != hipSuccess)
         return bfail(b, STIXELS_E_HIP, "synchronising the capture stream failed");
@@ -388,12 +440,8 @@ int stixels_batch_capture(stixels_batch* b, const stixels_job* jobs, int32_t n, 
     destroy_graph(b);
     if (hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) != hipSuccess)
         return bfail(b, STIXELS_E_HIP, "hipStreamBeginCapture failed");
-    hipError_t e = launch_pose_tables(b->d_pose_items_g, b->npose, b->pose_hmax, st);
-    if (e == hipSuccess)
-        e = pairs ? launch_pair_batch(slots, nch, grid, st, b->d_jobs_g, b->d_tasks_g, ntasks,
-                                  b->d_counter_g, b->d_scratch, stride, hmax)
-              : launch_batch(slots, nch, waves, b->links, grid, st, b->d_jobs_g, b->d_tasks_g, ntasks,
-                             b->d_counter_g, b->d_scratch, stride, hmax);
+    const hipError_t e =
+        launch(b, p, b->d_jobs_g, b->d_tasks_g, b->d_counter_g, b->d_pose_items_g, st);
     hipGraph_t g = nullptr;
     const hipError_t e2 = hipStreamEndCapture(st, &g);
     if (e != hipSuccess || e2 != hipSuccess || !g) {
@@ -405,10 +453,7 @@ int stixels_batch_capture(stixels_batch* b, const stixels_job* jobs, int32_t n, 
         destroy_graph(b);
         return bfail(b, STIXELS_E_HIP, "hipGraphInstantiate failed");
     }
-    b->last_grid = grid;
-    b->last_tasks = ntasks;
-    b->last_waves = waves;
-    b->last_columns = pairs ? 2 : 1;
+    remember(b, p);
     return STIXELS_OK;
 }
 
@@ -429,7 +474,7 @@ int stixels_batch_set_workgroups(stixels_batch* b, int32_t workgroups) {
 int stixels_batch_set_waves(stixels_batch* b, int32_t waves) {
     if (!b || (waves != 0 && waves != 1 && waves != 2 && waves != 4))
         return bfail(b, STIXELS_E_INVALID_ARG, "waves per column must be 0, 1, 2 or 4");
-    b->waves = waves == 0 ? 1 : waves;
+    b->waves = waves;
     return STIXELS_OK;
 }
 

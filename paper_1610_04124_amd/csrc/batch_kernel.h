@@ -31,6 +31,7 @@ struct JobDesc {
     const float* ground;
     const float* object_t;
     const float* object_df;
+    const float* object_min;
     const int32_t* fg_hi;
     const int32_t* fg_lo;
     int32_t* counts;

@@ -256,17 +256,20 @@ __device__ __forceinline__ void chain_prep(const ChainCol& c, const ChainLds& L,
     }
 }
 
-// bound[i][j] = min over f of the object cost of rows [i B, j B) at mean f (no
-// stixel costs those rows less), from the column's table of prefixes at block
-// boundaries (edge, rows of kEdgeFloats).  The rows are staged in LDS (in the
-// ring's and the records' place, both unused yet); a lane takes one i and four
-// neighbouring j, a wave 64 such lanes and a part of the means; the parts'
-// minima meet in LDS (bound holds +inf before).  Called by every wave.
-__device__ __forceinline__ void chain_bounds(const ChainCol& c, const ChainLds& L,
-                                             const float* edge, const int wave, const int nw) {
+// The column's prefixes at block boundaries, while the bounds are made: rows of
+// 4 (H / 128 + 1) floats in LDS, in the ring's and the records' place (both
+// unused yet).
+__device__ __forceinline__ int chain_edge_quads(int H) { return H / kBlock / 4 + 1; }
+__device__ __forceinline__ float* chain_edges(const ChainLds& L) {
+    return reinterpret_cast<float*>(L.ring);
+}
+
+// Stages them from the table of entries 32 i (rows of kEdgeFloats).
+__device__ __forceinline__ void chain_load_edges(const ChainCol& c, const ChainLds& L,
+                                                 const float* edge, const int wave, const int nw) {
     const int lane = threadIdx.x & 63;
-    const int nb = c.H / kBlock, nq = nb / 4 + 1;     // last boundary, quads of boundaries
-    float* const tile = reinterpret_cast<float*>(L.ring);
+    const int nb = c.H / kBlock, nq = chain_edge_quads(c.H);
+    float* const tile = chain_edges(L);
     const auto er = make_rsrc(edge, (uint32_t)(c.nrow * kEdgeFloats) * 4u);
     const uint32_t off = (uint32_t)min(lane, nb) * 4u;
     constexpr int U = 8;
@@ -279,7 +282,17 @@ __device__ __forceinline__ void chain_bounds(const ChainCol& c, const ChainLds& 
         for (int u = 0; u < U; ++u)
             if (lane < 4 * nq && f0 + u * nw < c.nrow) tile[(f0 + u * nw) * 4 * nq + lane] = x[u];
     }
-    __syncthreads();
+}
+
+// bound[i][j] = min over f of the object cost of rows [i B, j B) at mean f (no
+// stixel costs those rows less) from the staged edges.  A lane takes one i and
+// four neighbouring j, a wave 64 such lanes and a part of the means; the parts'
+// minima meet in LDS (bound holds +inf before).
+__device__ __forceinline__ void chain_bounds(const ChainCol& c, const ChainLds& L, const int wave,
+                                             const int nw) {
+    const int lane = threadIdx.x & 63;
+    const int nb = c.H / kBlock, nq = chain_edge_quads(c.H);
+    const float* const tile = chain_edges(L);
     const int items = (nb + 1) * nq, sets = (items + 63) >> 6, parts = max(nw / sets, 1);
     for (int w = wave; w < sets * parts; w += nw) {
         const int set = w % sets, part = w / sets;
@@ -444,13 +457,13 @@ __device__ __forceinline__ bool chain_run(const ChainCol& c, const ChainLds& L, 
     // the operands of the eight steps ahead of each step
     float4 o[kGroup];
     auto fetch = [&](int u, int G) {
-        o[u] = L.ring[((G & (kRing - 1)) * kGroup + u) * 64 + lane];
+        o[u] = L.ring[((G % kRing) * kGroup + u) * 64 + lane];
     };
     // flags of a group and the far candidates they guard (read in this order)
     int fprep, ffar0, ffar1;
     float4 far;
     auto peek = [&](int G) {
-        fprep = flag_peek(&L.fl->prep[(G + 1) & (kRing - 1)]);
+        fprep = flag_peek(&L.fl->prep[(G + 1) % kRing]);
         ffar0 = flag_peek(&L.fl->far[G >> 3][0]);
         ffar1 = flag_peek(&L.fl->far[G >> 3][1]);
         lds_order();
@@ -659,46 +672,44 @@ __device__ __forceinline__ void chain_backtrack(const ChainCol& c, const ChainLd
     }
 }
 
-// One column by the whole workgroup (chain_waves(H) waves).  lds: 16-byte
-// aligned, chain_lds_bytes(H).  The column's prefix tables (in) are in memory
-// that every wave can read.  Results are written by wave 0; the LDS may be
-// reused after a barrier.
-__device__ __forceinline__ void solve_chain(const int H, const int vtop, const Prior& P,
-                                            const ColumnIn& in, const ColumnOut& out, char* lds) {
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int nw = (int)(blockDim.x >> 6);
-    const ChainLds L = chain_lds(lds, H);
+// A column for the chain's waves: its object prefix table (rows of stride4
+// bytes, row f - fbase) and constants.
+__device__ __forceinline__ ChainCol chain_column(const int H, const int vtop, const Prior& P,
+                                                 const float* PO, const int fbase, const int fmax,
+                                                 const uint32_t stride4) {
     ChainCol c;
     c.H = H;
     c.vtop = vtop;
-    c.fbase = in.fbase;
-    c.nrow = in.fmax - in.fbase + 1;
-    c.stride4 = (uint32_t)(in.po_stride ? in.po_stride : H + 1) * 4u;
-    c.po = make_rsrc(in.PO, (uint32_t)c.nrow * c.stride4);
+    c.fbase = fbase;
+    c.nrow = fmax - fbase + 1;
+    c.stride4 = stride4;
+    c.po = make_rsrc(PO, (uint32_t)c.nrow * stride4);
     c.eps = P.mean_eps;
     c.T00 = P.trans[0][0];
+    c.T00c = P.trans[0][0] + P.c_ord;
     c.T10 = P.trans[1][0];
     c.T20 = P.trans[2][0];
-    c.T00c = P.trans[0][0] + P.c_ord;
     c.c_grav = P.c_grav;
     c.c_dive = P.c_dive;
-    const float INF = inf_f();
+    return c;
+}
+
+// Clears the flags and bounds (by every thread, ahead of a barrier).
+__device__ __forceinline__ void chain_clear(const ChainLds& L) {
     if (threadIdx.x < sizeof(ChainFlags) / 4) reinterpret_cast<int*>(L.fl)[threadIdx.x] = 0;
     for (int i = threadIdx.x; i < kBoundStride * kBoundStride; i += (int)blockDim.x)
-        L.bound[i] = INF;
-    for (int b = threadIdx.x; b <= H; b += (int)blockDim.x) {
-        const int r = max(H - 1 - b, 0);
-        L.base[b] = make_float4(in.PA[b], in.PN2[b], __builtin_bit_cast(float, in.fg_hi[r]),
-                                __builtin_bit_cast(float, in.fg_lo[r]));
-        L.pre[b] = make_float4(in.PG[b], in.PS[b], in.PM[b], 0.0f);
-    }
-    if (H > 64) {
-        __syncthreads();
-        chain_bounds(c, L, in.PO_edge, wave, nw);
-    }
-    __syncthreads();
-    const int slots = (H + 63) >> 6;
+        L.bound[i] = inf_f();
+}
+
+// One column by the whole workgroup (chain_waves(H, ..) waves), its base, pre
+// and bound arrays filled and its flags cleared.  Results are written by wave
+// 0; the LDS may be reused after a barrier.
+__device__ __forceinline__ void chain_solve(const ChainCol& c, const ChainLds& L, const Prior& P,
+                                            const ColumnOut& out) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int nw = (int)(blockDim.x >> 6);
+    const int slots = (c.H + 63) >> 6;
     if (wave == 0) {
         __builtin_amdgcn_s_setprio(3);
         const bool ok = chain_run(c, L, P);
@@ -707,7 +718,7 @@ __device__ __forceinline__ void solve_chain(const int H, const int vtop, const P
             chain_backtrack(c, L, P, out);
         } else if (lane == 0) {
             *out.count = 0;
-            *out.total = INF;
+            *out.total = inf_f();
             *out.overflow = 255;
         }
     } else if (wave <= kPrepWaves) {
@@ -726,6 +737,31 @@ __device__ __forceinline__ void solve_chain(const int H, const int vtop, const P
         bool ok = true;
         for (int t = f; ok && t < 2 * slots; t += nf) ok = chain_far(c, L, P, t >> 1, t & 1);
     }
+}
+
+// One column from its prefix tables in memory (in).  lds: 16-byte aligned,
+// chain_lds_bytes(H).
+__device__ __forceinline__ void solve_chain(const int H, const int vtop, const Prior& P,
+                                            const ColumnIn& in, const ColumnOut& out, char* lds) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int nw = (int)(blockDim.x >> 6);
+    const ChainLds L = chain_lds(lds, H);
+    const ChainCol c = chain_column(H, vtop, P, in.PO, in.fbase, in.fmax,
+                                    (uint32_t)in.po_stride * 4u);
+    chain_clear(L);
+    for (int b = threadIdx.x; b <= H; b += (int)blockDim.x) {
+        const int r = max(H - 1 - b, 0);
+        L.base[b] = make_float4(in.PA[b], in.PN2[b], __builtin_bit_cast(float, in.fg_hi[r]),
+                                __builtin_bit_cast(float, in.fg_lo[r]));
+        L.pre[b] = make_float4(in.PG[b], in.PS[b], in.PM[b], 0.0f);
+    }
+    if (H > 64) {
+        chain_load_edges(c, L, in.PO_edge, wave, nw);
+        __syncthreads();
+        chain_bounds(c, L, wave, nw);
+    }
+    __syncthreads();
+    chain_solve(c, L, P, out);
 }
 
 }  // namespace stx

@@ -17,6 +17,7 @@ inline JobDesc make_job_desc(const stixels_handle* h, const float* disp, int W, 
     d.ground = h->d_ground;
     d.object_t = h->d_object_t;
     d.object_df = h->d_object_df;
+    d.object_min = h->d_object_min;
     d.fg_hi = h->d_fg_hi;
     d.fg_lo = h->d_fg_lo;
     d.counts = out.counts;

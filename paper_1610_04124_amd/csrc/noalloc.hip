@@ -8,6 +8,7 @@
 #include <mutex>
 #include <string>
 
+#include "chain_frame.h"
 #include "handle.h"
 #include "job_desc.h"
 #include "launch.h"
@@ -87,7 +88,10 @@ extern "C" int stixels_compute_noalloc(stixels_handle* h, const float* d_dispari
     persist::JobDesc job = persist::make_job_desc(h, d_disparity, width, height, *out);
     const int waves = frame_waves(h->waves, height, ncols, h->num_cu);
     int grid = 0;
-    e = persist::launch_frame_fused(job, ws, kNoAllocScratchBytes, waves, h->num_cu, st, &grid);
+    if (h->prior.exact && h->waves == 0)
+        e = persist::launch_chain_arena(job, ws, kNoAllocScratchBytes, h->num_cu, st);
+    else
+        e = persist::launch_frame_fused(job, ws, kNoAllocScratchBytes, waves, h->num_cu, st, &grid);
     if (e != hipSuccess)
         return set_err(h, STIXELS_E_HIP, std::string("kernel launch failed: ") + hipGetErrorString(e));
     return STIXELS_OK;

@@ -88,13 +88,12 @@ class GpuExecutor:
         self._torch = torch
         self._P = P
         # launch layout of each height class: (columns per wave, waves per
-        # column, workgroups); untuned classes use one wave per column for
-        # up to 8 slots and two above, the autotuner's choice at 440 and 880
-        # rows on MI355X, and the occupancy limit
+        # column, workgroups); untuned classes leave the waves to the library
+        # (by rows and columns of each launch) and use the occupancy limit
         self.layout = {}
 
     def layout_for(self, k: int):
-        return self.layout.get(k, (1, 1 if k <= 8 else 2, 0))
+        return self.layout.get(k, (1, 0, 0))
 
     def resident_bytes(self) -> int:
         """Device bytes held for the whole run: the batch objects and the

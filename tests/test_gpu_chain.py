@@ -78,3 +78,35 @@ def test_chain_priors_and_capacity():
     assert_frames_equal(gpu_frame(h, disp), ref, "free transitions")
     assert_frames_equal(gpu_frame(h, disp, capacity=5), oracle.frame(p, disp, cap=5), "capacity")
     h.close()
+
+
+@pytest.mark.parametrize("heights", [(64, 65, 440), (1024, 7, 513, 128), (512, 300)])
+def test_chain_batch_mixed(heights):
+    """Frames of several heights, disparity ranges and column counts in one
+    automatic launch (more columns than workgroups, so that workgroups go from
+    one column to another of a different height), captured and replayed."""
+    import torch
+    announce(f"chain batch {heights}")
+    st = torch.cuda.Stream()
+    items, refs = [], []
+    for i, H in enumerate(heights):
+        p, disp = frame_and_params(H, (64, 128, 256)[i % 3], ("columns", "object steps")[i % 2],
+                                   s=2, cols=250)
+        h = P.Stixels(dict(p, flags=1))
+        t = torch.from_numpy(np.ascontiguousarray(disp)).cuda()
+        items.append((h, t, h.new_output(disp.shape[1], H)))
+        refs.append(oracle.frame(p, disp))
+    torch.cuda.synchronize()
+    b = P.Batch(len(items), 250 * len(items), max(heights), 256)
+    b.capture(items, st)
+    assert b.waves() > 4                  # a workgroup per column
+    for _ in range(3):
+        for _, _, o in items:
+            o.counts.zero_()
+            o.records.zero_()
+        torch.cuda.synchronize()
+        b.replay(st)
+        torch.cuda.synchronize()
+        for (_, _, o), ref, H in zip(items, refs, heights):
+            assert_frames_equal(o.to_host(), ref, f"batch {H}")
+    b.close()
