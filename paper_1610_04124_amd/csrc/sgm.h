@@ -8,12 +8,16 @@
 namespace stx::sgm {
 
 // Device workspace of a matching handle, sized for max_frames frames of
-// max_width x max_height: census words of both views, and the summed path
-// costs S [frame][y][x][d] (uint16).
+// max_width x max_height: census words of both views, and either planes of path
+// costs in bytes, [direction][frame][y][x][d] of the call's size, or their sums
+// S [frame][y][x][d] (uint16).
 struct SgmWorkspace {
     uint64_t* cl = nullptr;
     uint64_t* cr = nullptr;
     uint16_t* S = nullptr;
+    uint8_t* planes = nullptr;
+    size_t plane_bytes = 0;         // of all planes
+    int num_cu = 0;
 };
 
 struct PathArgs {
@@ -26,6 +30,15 @@ struct PathArgs {
 
 // Disparities per lane of a path wave for D disparities (D <= 64 DPL).
 int dpl_of(int D);
+
+// Whether path costs fit a byte under this penalty; whether a call's lines are
+// few enough that all four directions go to planes (else three); and the path
+// passes with costs in bytes (sgm_packed.hip).
+bool packed_costs(int P2);
+bool packed_four(int D, int H, int frames, int num_cu);
+hipError_t launch_packed_paths(const uint64_t* cl, const uint64_t* cr, uint8_t* planes,
+                               size_t plane, bool four, int W, int H, int frames, int D, int P1,
+                               int P2, float* disp, hipStream_t st);
 
 // The whole stage over `frames` frames stored back to back ([frame][H][W]
 // uint8 images, [frame][H][W] float disparity out); enqueued on st.

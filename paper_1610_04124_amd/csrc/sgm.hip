@@ -16,7 +16,11 @@
 //            minimising S((y, x + d), d); left-right check |d_L - d_R| <= 1,
 //            else -1 (the stixel input's invalid value)
 //
-// Work distribution: one wave64 per path line (an image row for the two
+// The path passes below serve penalties whose path costs exceed a byte (P2 >
+// 193) and handles whose planes of bytes found no memory; all others are
+// sgm_packed.hip's.
+//
+// Work distribution here: one wave64 per path line (an image row for the two
 // horizontal directions, a column for the two vertical ones), lanes over
 // disparities (lane l owns DPL consecutive disparities l DPL + i), steps
 // along the line.  A step's neighbour terms d -+ 1 cross lanes by one DPP
@@ -34,6 +38,7 @@
 #include <new>
 #include <string>
 #include <type_traits>
+#include <vector>
 
 #include "handle.h"
 #include "internal.h"
@@ -576,6 +581,12 @@ hipError_t launch_sgm(const uint8_t* left, const uint8_t* right, int W, int H, i
     hipLaunchKernelGGL(census_kernel, grid, dim3(256), 0, st, left, right, W, H, ws.cl, ws.cr);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (ws.planes) {
+        const size_t plane = (size_t)frames * W * H * D;
+        const bool four = 4 * plane <= ws.plane_bytes && packed_four(D, H, frames, ws.num_cu);
+        return launch_packed_paths(ws.cl, ws.cr, ws.planes, plane, four, W, H, frames, D, P1, P2,
+                                   disp, st);
+    }
     PathArgs a{ws.cl, ws.cr, ws.S, disp, W, H, D, P1, P2};
     switch (dpl_of(D)) {
         case 1: return launch_paths<1>(a, frames, st);
@@ -591,7 +602,7 @@ struct stixels_sgm {
     stixels_sgm_params p{};
     stx::sgm::SgmWorkspace ws{};
     size_t bytes = 0;
-    int last_W = 0, last_H = 0, device = 0;
+    int last_W = 0, last_H = 0, last_frames = 0, device = 0;
     std::string err;
 };
 
@@ -631,13 +642,30 @@ int stixels_sgm_create(const stixels_sgm_params* params, stixels_sgm** out) {
     const size_t n = (size_t)p.max_frames * (size_t)p.max_width * (size_t)p.max_height;
     const size_t nd = n * (size_t)p.max_disparity;
     bool ok = hipMalloc(reinterpret_cast<void**>(&m->ws.cl), n * sizeof(uint64_t)) == hipSuccess &&
-              hipMalloc(reinterpret_cast<void**>(&m->ws.cr), n * sizeof(uint64_t)) == hipSuccess &&
-              hipMalloc(reinterpret_cast<void**>(&m->ws.S), nd * sizeof(uint16_t)) == hipSuccess;
-    m->bytes = 2 * n * sizeof(uint64_t) + nd * sizeof(uint16_t);
+              hipMalloc(reinterpret_cast<void**>(&m->ws.cr), n * sizeof(uint64_t)) == hipSuccess;
+    m->bytes = 2 * n * sizeof(uint64_t);
+    // planes of bytes where the penalties allow them and the memory is there
+    // (three, or four if the largest call's lines are few), else 16-bit sums
+    if (hipDeviceGetAttribute(&m->ws.num_cu, hipDeviceAttributeMultiprocessorCount, m->device) !=
+        hipSuccess)
+        m->ws.num_cu = 0;
+    const size_t planes =
+        nd * (stx::sgm::packed_four(p.max_disparity, p.max_height, p.max_frames, m->ws.num_cu) ? 4 : 3);
+    if (ok && stx::sgm::packed_costs(p.p2) &&
+        hipMalloc(reinterpret_cast<void**>(&m->ws.planes), planes) == hipSuccess) {
+        m->ws.plane_bytes = planes;
+        m->bytes += planes;
+    } else if (ok) {
+        (void)hipGetLastError();
+        m->ws.planes = nullptr;
+        ok = hipMalloc(reinterpret_cast<void**>(&m->ws.S), nd * sizeof(uint16_t)) == hipSuccess;
+        m->bytes += nd * sizeof(uint16_t);
+    }
     if (!ok) {
         (void)hipFree(m->ws.cl);
         (void)hipFree(m->ws.cr);
         (void)hipFree(m->ws.S);
+        (void)hipFree(m->ws.planes);
         delete m;
         g_sgm_create_error = "hipMalloc of the matching workspace failed";
         return STIXELS_E_NOMEM;
@@ -651,6 +679,7 @@ int stixels_sgm_destroy(stixels_sgm* m) {
     (void)hipFree(m->ws.cl);
     (void)hipFree(m->ws.cr);
     (void)hipFree(m->ws.S);
+    (void)hipFree(m->ws.planes);
     delete m;
     return STIXELS_OK;
 }
@@ -682,6 +711,7 @@ int stixels_sgm_compute(stixels_sgm* m, const uint8_t* d_left, const uint8_t* d_
         return sgm_fail(m, STIXELS_E_HIP, std::string("kernel launch failed: ") + hipGetErrorString(e));
     m->last_W = width;
     m->last_H = height;
+    m->last_frames = frames;
     return STIXELS_OK;
 }
 
@@ -694,6 +724,26 @@ int stixels_sgm_debug(const stixels_sgm* m, int32_t which, void* host_dst, size_
     const size_t need = which == 2 ? n * (size_t)m->p.max_disparity * sizeof(uint16_t)
                                    : n * sizeof(uint64_t);
     if (bytes < need) return STIXELS_E_INVALID_ARG;
+    if (which == 2 && m->ws.planes) {
+        // the sums of the three planes of frame 0
+        const size_t nd = n * (size_t)m->p.max_disparity;
+        std::vector<uint8_t> plane;
+        try {
+            plane.resize(nd);
+        } catch (const std::bad_alloc&) {
+            return STIXELS_E_NOMEM;
+        }
+        uint16_t* const dst = static_cast<uint16_t*>(host_dst);
+        if (hipDeviceSynchronize() != hipSuccess) return STIXELS_E_HIP;
+        for (int r = 0; r < 3; ++r) {
+            if (hipMemcpy(plane.data(), m->ws.planes + (size_t)(r * m->last_frames) * nd, nd,
+                          hipMemcpyDeviceToHost) != hipSuccess)
+                return STIXELS_E_HIP;
+            for (size_t i = 0; i < nd; ++i)
+                dst[i] = (uint16_t)((r ? dst[i] : 0) + plane[i]);
+        }
+        return STIXELS_OK;
+    }
     if (hipDeviceSynchronize() != hipSuccess ||
         hipMemcpy(host_dst, src, need, hipMemcpyDeviceToHost) != hipSuccess)
         return STIXELS_E_HIP;
