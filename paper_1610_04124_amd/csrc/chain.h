@@ -230,12 +230,18 @@ __device__ __forceinline__ void chain_prep(const ChainCol& c, const ChainLds& L,
         float4 bs[kGroup];                            // read together: one LDS latency
 #pragma unroll
         for (int u = 0; u < kGroup; ++u) bs[u] = L.base[min(j0 + u + 1, c.H - 1)];
+        auto pairs = [&](auto GR) {
 #pragma unroll
-        for (int u = 0; u < kGroup; ++u) {
-            const bool up = lane <= jl0 + u;          // the lane has moved on to the next slot
-            const int b = min(j0 + u + 1, c.H - 1);
-            r[u] = chain_pair<true>(c, bs[u], b, up ? e1.x : e0.x, up ? e1.y : e0.y, up ? o1 : o0);
-        }
+            for (int u = 0; u < kGroup; ++u) {
+                const bool up = lane <= jl0 + u;      // the lane has moved on to the next slot
+                const int b = min(j0 + u + 1, c.H - 1);
+                r[u] = chain_pair<decltype(GR)::value>(c, bs[u], b, up ? e1.x : e0.x,
+                                                       up ? e1.y : e0.y, up ? o1 : o0);
+            }
+        };
+        // above vtop no ground stixel precedes (C_g is INF there)
+        if (j0 <= c.vtop) pairs(std::true_type{});
+        else pairs(std::false_type{});
         // each row's ground (even lanes; INF above vtop) or sky cost
         float ec[kGroup], pp[kGroup + 1];
 #pragma unroll
@@ -394,9 +400,16 @@ __device__ __forceinline__ bool chain_far(const ChainCol& c, const ChainLds& L, 
         float4 bs[kGroup];
 #pragma unroll
         for (int u = 0; u < kGroup; ++u) bs[u] = L.base[8 * g + 1 + u];
+        // above vtop no ground stixel precedes (C_g is INF there)
+        if (8 * g <= c.vtop) {
 #pragma unroll
-        for (int u = 0; u < kGroup; ++u)
-            r[u] = chain_pair<true>(c, bs[u], 8 * g + 1 + u, e.x, e.y, koff);
+            for (int u = 0; u < kGroup; ++u)
+                r[u] = chain_pair<true>(c, bs[u], 8 * g + 1 + u, e.x, e.y, koff);
+        } else {
+#pragma unroll
+            for (int u = 0; u < kGroup; ++u)
+                r[u] = chain_pair<false>(c, bs[u], 8 * g + 1 + u, e.x, e.y, koff);
+        }
     };
     auto finish = [&](const ChainPair (&r)[kGroup], int g, bool use) -> bool {
         if (use) {
@@ -703,9 +716,10 @@ __device__ __forceinline__ void chain_clear(const ChainLds& L) {
 
 // One column by the whole workgroup (chain_waves(H, ..) waves), its base, pre
 // and bound arrays filled and its flags cleared.  Results are written by wave
-// 0; the LDS may be reused after a barrier.
+// 0, to where get_out() says then; the LDS may be reused after a barrier.
+template <class Out>
 __device__ __forceinline__ void chain_solve(const ChainCol& c, const ChainLds& L, const Prior& P,
-                                            const ColumnOut& out) {
+                                            Out&& get_out) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int nw = (int)(blockDim.x >> 6);
@@ -714,6 +728,7 @@ __device__ __forceinline__ void chain_solve(const ChainCol& c, const ChainLds& L
         __builtin_amdgcn_s_setprio(3);
         const bool ok = chain_run(c, L, P);
         __builtin_amdgcn_s_setprio(0);
+        const ColumnOut out = get_out();
         if (ok) {
             chain_backtrack(c, L, P, out);
         } else if (lane == 0) {
@@ -761,7 +776,7 @@ __device__ __forceinline__ void solve_chain(const int H, const int vtop, const P
         chain_bounds(c, L, wave, nw);
     }
     __syncthreads();
-    chain_solve(c, L, P, out);
+    chain_solve(c, L, P, [&]() { return out; });
 }
 
 }  // namespace stx

@@ -39,6 +39,35 @@ struct ChainArgs {
     unsigned int room4;          // kArena: 16-byte units of table space
 };
 
+// The kernel's arguments and the jobs are read where they are used, through
+// the scalar cache: kept over a column (or over the loop of columns) they fill
+// the scalar registers, whose overflow then fills the vector registers, inside
+// the recurrence's loops (the batch form spilled 31 and the workspace form 81
+// vector registers, now 9 and 7: 64 uneven frames 4,170 -> 3,644 us, 1024x437
+// at half pixels in a workspace 96 -> 73).
+template <class T>
+using Const = const __attribute__((address_space(4))) T*;
+template <class T>
+__device__ __forceinline__ Const<T> in_const(const T* p) {
+    return (Const<T>)reinterpret_cast<uintptr_t>(p);
+}
+// p, with everything read through it so far forgotten
+template <class T>
+__device__ __forceinline__ Const<T> again(Const<T> p) {
+    asm volatile("" : "+s"(p));
+    return p;
+}
+template <class T>
+__device__ __forceinline__ T load_const(Const<T> p) {
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    struct Words {
+        uint32_t w[sizeof(T) / 4];
+    } x;
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(T) / 4); ++i) x.w[i] = ((Const<uint32_t>)p)[i];
+    return __builtin_bit_cast(T, x);
+}
+
 // LDS besides the chain's: the overlay of the ring and records holds, until
 // the chain starts, the edges (D rows), a staged cost row per wave and the
 // column's pixels.
@@ -57,10 +86,11 @@ __host__ __device__ constexpr int lds_bytes(int H, int D, int nw) {
 
 // Small prefix table t of a column from its pixels (one wave): entries into a
 // component of an LDS float4 array, and to memory when out is given.
-__device__ __forceinline__ void small_table(const JobDesc& J, const int16_t* qs, const int t,
+__device__ __forceinline__ void small_table(Const<JobDesc> J, const int16_t* qs, const int t,
                                             float* dst, float* out) {
     const int lane = threadIdx.x & 63;
-    const int H = J.H, D = J.D;
+    const int H = J->H, D = J->D;
+    const float* const src = t == 0 ? J->ground : (t == 1 ? J->sky : J->object_min);
     if (lane == 0) {
         dst[0] = 0.0f;
         if (out) out[0] = 0.0f;
@@ -75,10 +105,9 @@ __device__ __forceinline__ void small_table(const JobDesc& J, const int16_t* qs,
             const int x = (v < H) ? (int)qs[v] : -1;
             r[i] = 0.0f;
             if (x >= 0) {
-                r[i] = (t == 0) ? J.ground[(size_t)(H - 1 - v) * D + x]
-                     : (t == 1) ? J.sky[x]
-                     : (t == 2) ? (float)(2 * x + 1)
-                     : (t == 3) ? 2.0f : J.object_min[x];
+                r[i] = (t == 2) ? (float)(2 * x + 1)
+                     : (t == 3) ? 2.0f
+                                : src[(t == 0) ? (size_t)(H - 1 - v) * D + x : (size_t)x];
             }
         }
         r[1] += r[0];
@@ -102,14 +131,14 @@ __device__ __forceinline__ void small_table(const JobDesc& J, const int16_t* qs,
 // (*next, in LDS): as in the staged table kernel, with the entries 32 i into
 // the staged edges.  NU: 256-row groups.
 template <int NU>
-__device__ __forceinline__ void object_rows(const JobDesc& J, const int16_t* qs, float* stg,
+__device__ __forceinline__ void object_rows(Const<JobDesc> J, const int16_t* qs, float* stg,
                                             float* edges, int* next, float* PO, const int fmin,
                                             const int fmax) {
     constexpr int NC = kMaxDisparity / 64;
     const int lane = threadIdx.x & 63;
-    const int H = J.H, D = J.D, nch = (D + 63) >> 6, nq4 = 4 * chain_edge_quads(H);
+    const int H = J->H, D = J->D, nch = (D + 63) >> 6, nq4 = 4 * chain_edge_quads(H);
     const uint32_t stride4 = (uint32_t)po_row_floats(H) * 4u;
-    const auto otr = make_rsrc(J.object_t, (uint32_t)(D * D) * 4u);
+    const auto otr = make_rsrc(J->object_t, (uint32_t)(D * D) * 4u);
     const auto pow_ = make_rsrc(PO, (uint32_t)(fmax - fmin + 1) * stride4);
     if (lane == 0) stg[D] = 0.0f;
     int qi[NU][4];                               // stage index of each row's cost
@@ -174,40 +203,44 @@ __device__ __forceinline__ void object_rows(const JobDesc& J, const int16_t* qs,
 
 template <int MODE>
 __global__ __launch_bounds__(64 * kChainWaves)
-__attribute__((amdgpu_waves_per_eu(4))) void chain_frame_kernel(const ChainArgs a) {
+__attribute__((amdgpu_waves_per_eu(4))) void chain_frame_kernel(const ChainArgs) {
     extern __shared__ __align__(16) char mem[];
     __shared__ int red[4];                       // smallest, largest, any invalid; next object row
     __shared__ int task;
-    __shared__ float* place;
+    __shared__ unsigned int place;               // kArena: in 16-byte units
+    constexpr unsigned int kNoPlace = ~0u;
+    // the arguments where they lie
+    const Const<ChainArgs> a = (Const<ChainArgs>)__builtin_amdgcn_kernarg_segment_ptr();
     const int tid = threadIdx.x, lane = tid & 63, nt = (int)blockDim.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = nt >> 6;
-    float* own = nullptr;                        // kArena: this workgroup's table space
-    unsigned int own4 = 0;
+    unsigned int own = 0, own4 = 0;              // kArena: this workgroup's table space
     for (bool once = true; MODE != kFrame || once; once = false) {
         int job = 0, col = (int)blockIdx.x;
         if constexpr (MODE != kFrame) {
             if (tid == 0) {
-                unsigned int* const c = MODE == kBatch ? a.counter
-                                      : (MODE == kArena ? &a.head->next : &a.head->next_rest);
+                const Const<ChainArgs> A = again(a);
+                unsigned int* const c = MODE == kBatch ? A->counter
+                                      : (MODE == kArena ? &A->head->next : &A->head->next_rest);
                 task = (int)atomicAdd(c, 1u);
             }
             __syncthreads();
             const int t = __builtin_amdgcn_readfirstlane(task);
             if constexpr (MODE == kBatch) {
-                if (t >= a.ntasks) break;
-                const int2 tk = a.tasks[t];
-                job = tk.x;
-                col = tk.y;
+                if (t >= again(a)->ntasks) break;
+                const Const<int> tk = in_const(reinterpret_cast<const int*>(again(a)->tasks)) + 2 * t;
+                job = tk[0];
+                col = tk[1];
             } else if constexpr (MODE == kArena) {
-                if (t >= a.job.ncols) break;
+                if (t >= again(a)->job.ncols) break;
                 col = t;
             } else {
-                if (t >= (int)a.head->nrest) break;
-                col = a.rest[t];
+                const Const<ChainArgs> A = again(a);
+                if (t >= __builtin_amdgcn_readfirstlane((int)A->head->nrest)) break;
+                col = __builtin_amdgcn_readfirstlane(A->rest[t]);
             }
         }
-        const JobDesc& J = MODE == kBatch ? a.jobs[job] : a.job;
-        const int H = J.H, D = J.D, stride = H + 1;
+        const Const<JobDesc> job_at = MODE == kBatch ? in_const(again(a)->jobs) + job : &a->job;
+        const int H = job_at->H, D = job_at->D, stride = H + 1;
         ChainLds L = chain_lds(mem, H);
         {   // the overlay may need more room than the ring and the records
             const int more = overlay_bytes(H, D, nw) - ring_rec_bytes(H);
@@ -226,12 +259,13 @@ __attribute__((amdgpu_waves_per_eu(4))) void chain_frame_kernel(const ChainArgs 
         // Sec. 4.1: the column's strips, bottom-up
         int lmin = INT_MAX, lmax = -1;
         bool inv = false;
+        const Const<JobDesc> J = again(job_at);
         for (int v = tid; v < H; v += nt) {
-            const int x = reduce_any(J.disp + (size_t)(H - 1 - v) * J.W + (size_t)col * J.s, J.s,
-                                     J.reduce_mode, D, J.sub);
+            const int x = reduce_any(J->disp + (size_t)(H - 1 - v) * J->W + (size_t)col * J->s, J->s,
+                                     J->reduce_mode, D, J->sub);
             qs[v] = (int16_t)x;
             if constexpr (MODE == kFrame) {
-                if (a.ex.q) a.ex.q[(size_t)col * H + v] = (int16_t)x;
+                if (a->ex.q) a->ex.q[(size_t)col * H + v] = (int16_t)x;
             }
             if (x >= 0) {
                 lmin = min(lmin, x);
@@ -264,23 +298,26 @@ __attribute__((amdgpu_waves_per_eu(4))) void chain_frame_kernel(const ChainArgs 
             const unsigned int need4 = (unsigned int)((fmax - fmin + 1) * (po_row_floats(H) / 4));
             if (own4 < need4) {
                 if (tid == 0) {
-                    const unsigned int at = atomicAdd(&a.head->used4, need4);
-                    const bool ok = at + need4 <= a.room4 && at + need4 >= at;
-                    place = ok ? a.po + (size_t)at * 4 : nullptr;
-                    if (!ok) a.rest[atomicAdd(&a.head->nrest, 1u)] = col;
+                    const Const<ChainArgs> A = again(a);
+                    const unsigned int at = atomicAdd(&A->head->used4, need4);
+                    const bool ok = at + need4 <= A->room4 && at + need4 >= at;
+                    place = ok ? at : kNoPlace;
+                    if (!ok) A->rest[atomicAdd(&A->head->nrest, 1u)] = col;
                 }
                 __syncthreads();
-                if (place) {
-                    own = place;
+                const unsigned int at = (unsigned int)__builtin_amdgcn_readfirstlane((int)place);
+                const bool left = at == kNoPlace;
+                if (!left) {
+                    own = at;
                     own4 = need4;
                 }
-                const bool left = place == nullptr;
                 __syncthreads();                 // before the next column writes place
                 if (left) continue;
             }
-            po = own;
+            po = again(a)->po + (size_t)own * 4;
         } else {
-            po = a.po + (size_t)(MODE == kFrame ? col : (int)blockIdx.x) * (size_t)a.stride;
+            const Const<ChainArgs> A = again(a);
+            po = A->po + (size_t)(MODE == kFrame ? col : (int)blockIdx.x) * (size_t)A->stride;
         }
 
         // Sec. 4.2: the small tables by the first five waves, the thresholds by
@@ -290,42 +327,48 @@ __attribute__((amdgpu_waves_per_eu(4))) void chain_frame_kernel(const ChainArgs 
                                (t == 0 || t == 2 ? 0 : (t == 4 ? 2 : 1));
             float* out = nullptr;
             if constexpr (MODE == kFrame) {
-                if (a.ex.prefix && t < 4)
-                    out = a.ex.prefix + ((size_t)t * J.ncols + col) * stride;
+                if (a->ex.prefix && t < 4)
+                    out = a->ex.prefix + ((size_t)t * a->job.ncols + col) * stride;
             }
-            small_table(J, qs, t, dst, out);
+            small_table(again(job_at), qs, t, dst, out);
         }
+        const int32_t *const fg_hi = again(job_at)->fg_hi, *const fg_lo = again(job_at)->fg_lo;
         for (int b = tid; b <= H; b += nt) {
             const int r = max(H - 1 - b, 0);
-            L.base[b].z = __builtin_bit_cast(float, J.fg_hi[r]);
-            L.base[b].w = __builtin_bit_cast(float, J.fg_lo[r]);
+            L.base[b].z = __builtin_bit_cast(float, fg_hi[r]);
+            L.base[b].w = __builtin_bit_cast(float, fg_lo[r]);
         }
         if constexpr (MODE == kFrame) {
-            if (a.ex.range && tid == 0) {
-                a.ex.range[2 * col] = fmin;
-                a.ex.range[2 * col + 1] = fmax;
+            if (a->ex.range && tid == 0) {
+                a->ex.range[2 * col] = fmin;
+                a->ex.range[2 * col + 1] = fmax;
             }
         }
         float* const stg = stage + wave * (kMaxDisparity + 4);
-        if (H <= 256) object_rows<1>(J, qs, stg, edges, &red[3], po, fmin, fmax);
-        else if (H <= 512) object_rows<2>(J, qs, stg, edges, &red[3], po, fmin, fmax);
-        else object_rows<4>(J, qs, stg, edges, &red[3], po, fmin, fmax);
+        if (H <= 256) object_rows<1>(again(job_at), qs, stg, edges, &red[3], po, fmin, fmax);
+        else if (H <= 512) object_rows<2>(again(job_at), qs, stg, edges, &red[3], po, fmin, fmax);
+        else object_rows<4>(again(job_at), qs, stg, edges, &red[3], po, fmin, fmax);
         __syncthreads();
 
         // Sec. 4.3-4.4
-        const ChainCol c = chain_column(H, J.vtop, J.prior, po + 3, fmin, fmax,
+        const Const<JobDesc> Jc = again(job_at);
+        const Prior prior = load_const(&Jc->prior);
+        const ChainCol c = chain_column(H, Jc->vtop, prior, po + 3, fmin, fmax,
                                         (uint32_t)po_row_floats(H) * 4u);
         if (H > 64) {
             chain_bounds(c, L, wave, nw);
             __syncthreads();
         }
-        ColumnOut out;
-        out.count = J.counts + col;
-        out.rec = J.records + (size_t)col * J.cap * 3;
-        out.total = J.total + col;
-        out.overflow = J.overflow + col;
-        out.cap = J.cap;
-        chain_solve(c, L, J.prior, out);
+        chain_solve(c, L, prior, [&]() {
+            const Const<JobDesc> J = again(job_at);
+            ColumnOut out;
+            out.count = J->counts + col;
+            out.rec = J->records + (size_t)col * J->cap * 3;
+            out.total = J->total + col;
+            out.overflow = J->overflow + col;
+            out.cap = J->cap;
+            return out;
+        });
         if constexpr (MODE != kFrame) __syncthreads();   // the next column reuses it all
     }
 }
