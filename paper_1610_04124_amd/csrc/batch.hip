@@ -17,8 +17,9 @@ using namespace stx;
 
 namespace stx::persist {
 
-// Resets the task counter before a launch (a kernel node, not a memset, so
-// that a captured graph replays it correctly).
+// Resets the task counter at the head of a captured launch (a kernel node, not
+// a memset, so that the graph replays it correctly); other launches upload a
+// zero with their descriptors.
 __global__ void reset_counter_kernel(unsigned int* c) { *c = 0u; }
 
 hipError_t launch_pair_batch(int slots, int nch, int grid, hipStream_t st, const JobDesc* jobs,
@@ -26,7 +27,6 @@ hipError_t launch_pair_batch(int slots, int nch, int grid, hipStream_t st, const
                              long long stride, int hmax) {
     const void* f = batch_pair_kernel_ptr(slots, nch);
     if (!f) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, st, counter);
     void* args[] = {&jobs, &tasks, &ntasks, &counter, &scratch, &stride, &hmax};
     return hipLaunchKernel(f, dim3(grid), dim3(64), args, 0, st);
 }
@@ -39,7 +39,6 @@ hipError_t launch_batch(int slots, int nch, int waves, bool links, int grid, hip
     // stagger the XCDs' starts only where the tasks fill two rounds or more
     // of the resident workgroups (a shorter launch would only be delayed)
     unsigned int stagger = (ntasks >= 2 * grid) ? kXcdStaggerCycles : 0u;
-    hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, st, counter);
     void* args[] = {&jobs, &tasks, &ntasks, &counter, &scratch, &stride, &hmax, &stagger};
     return hipLaunchKernel(f, dim3(grid), dim3(64 * waves), args, 0, st);
 }
@@ -51,17 +50,13 @@ using namespace stx::persist;
 struct stixels_batch {
     stixels_batch_config cfg{};
     int num_cu = 0;
-    // descriptors of the eager path and of the captured graph
-    JobDesc* d_jobs = nullptr;
-    int2* d_tasks = nullptr;
-    unsigned int* d_counter = nullptr;
-    JobDesc* d_jobs_g = nullptr;
-    int2* d_tasks_g = nullptr;
-    unsigned int* d_counter_g = nullptr;
+    // descriptor blocks (struct Block) of the eager path and of the captured
+    // graph, and their pinned staging, whose counter stays zero
+    char* d_block = nullptr;
+    char* d_block_g = nullptr;
+    char* h_block = nullptr;
     float* d_scratch = nullptr;
     size_t scratch_floats = 0;
-    JobDesc* h_jobs = nullptr;   // pinned staging
-    int2* h_tasks = nullptr;
     // frames with their own pose (STIXELS_BATCH_POSES): one ground table
     // area per job slot, and the table builds of the eager path and the graph
     char* d_pose_area = nullptr;
@@ -84,6 +79,20 @@ struct stixels_batch {
 };
 
 namespace {
+
+// A call's descriptors in one block, so that one copy takes them (and the
+// zero of the task counter) to the device: the counter, n jobs, the tasks.
+struct Block {
+    unsigned int* counter;
+    JobDesc* jobs;
+    int2* tasks;
+};
+constexpr size_t kBlockHead = 256;
+size_t tasks_at(int n) { return kBlockHead + ((sizeof(JobDesc) * (size_t)n + 15) & ~(size_t)15); }
+Block block_of(char* p, int n) {
+    return {reinterpret_cast<unsigned int*>(p), reinterpret_cast<JobDesc*>(p + kBlockHead),
+            reinterpret_cast<int2*>(p + tasks_at(n))};
+}
 
 int bfail(stixels_batch* b, int code, const std::string& m) {
     if (b) b->err = m;
@@ -153,6 +162,7 @@ int stage(stixels_batch* b, const stixels_job* jobs, int32_t n, int* slots, int*
             return bfail(b, STIXELS_E_HIP, "waiting for the previous upload failed");
         b->staged_pending = false;
     }
+    const Block hb = block_of(b->h_block, n);
     std::vector<int> order(n);
     for (int i = 0; i < n; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(),
@@ -163,8 +173,8 @@ int stage(stixels_batch* b, const stixels_job* jobs, int32_t n, int* slots, int*
     b->links = false;
     for (int i = 0; i < n; ++i) {
         const stixels_job& j = jobs[i];
-        b->h_jobs[i] = make_job_desc(j.handle, j.d_disparity, j.width, j.height, j.out);
-        b->h_jobs[i].phase = b->d_phase;
+        hb.jobs[i] = make_job_desc(j.handle, j.d_disparity, j.width, j.height, j.out);
+        hb.jobs[i].phase = b->d_phase;
         b->links = b->links || !j.handle->prior.exact;
         if (!j.use_pose) continue;
         if (!b->d_pose_area)
@@ -184,10 +194,10 @@ int stage(stixels_batch* b, const stixels_job* jobs, int32_t n, int* slots, int*
         if (rc != STIXELS_OK) return bfail(b, rc, "job " + std::to_string(i) + ": " + why);
         ++b->npose;
         b->pose_hmax = std::max(b->pose_hmax, (int)j.height);
-        b->h_jobs[i].ground = G;
-        b->h_jobs[i].fg_hi = hi;
-        b->h_jobs[i].fg_lo = lo;
-        b->h_jobs[i].vtop = ground_top(j.pose.horizon_row, j.height);
+        hb.jobs[i].ground = G;
+        hb.jobs[i].fg_hi = hi;
+        hb.jobs[i].fg_lo = lo;
+        hb.jobs[i].vtop = ground_top(j.pose.horizon_row, j.height);
     }
     // two columns per wave only where that kernel exists (h <= 512,
     // d_range <= 128); a task is then a (frame, even column) pair
@@ -195,8 +205,8 @@ int stage(stixels_batch* b, const stixels_job* jobs, int32_t n, int* slots, int*
                        kernel_chunks(dmax) == 2;
     for (int oi = 0; oi < n; ++oi) {
         const int i = order[oi];
-        const int nc = b->h_jobs[i].ncols;
-        for (int c = 0; c < nc; c += pairs ? 2 : 1) b->h_tasks[t++] = make_int2(i, c);
+        const int nc = hb.jobs[i].ncols;
+        for (int c = 0; c < nc; c += pairs ? 2 : 1) hb.tasks[t++] = make_int2(i, c);
     }
     *slots = kernel_slots(hmax);
     *nch = kernel_chunks(dmax);
@@ -233,12 +243,9 @@ int choose_grid(stixels_batch* b, int slots, int nch, int waves, bool pairs, lon
     return STIXELS_OK;
 }
 
-int upload(stixels_batch* b, JobDesc* dj, int2* dt, PoseItem* dp, int n, int ntasks,
-           hipStream_t st) {
-    if (hipMemcpyAsync(dj, b->h_jobs, sizeof(JobDesc) * n, hipMemcpyHostToDevice, st) !=
-            hipSuccess ||
-        hipMemcpyAsync(dt, b->h_tasks, sizeof(int2) * ntasks, hipMemcpyHostToDevice, st) !=
-            hipSuccess ||
+int upload(stixels_batch* b, char* block, PoseItem* dp, int n, int ntasks, hipStream_t st) {
+    if (hipMemcpyAsync(block, b->h_block, tasks_at(n) + sizeof(int2) * (size_t)ntasks,
+                       hipMemcpyHostToDevice, st) != hipSuccess ||
         (b->npose > 0 && hipMemcpyAsync(dp, b->h_pose_items, sizeof(PoseItem) * b->npose,
                                         hipMemcpyHostToDevice, st) != hipSuccess))
         return bfail(b, STIXELS_E_HIP, "descriptor upload failed");
@@ -277,12 +284,14 @@ int plan(stixels_batch* b, const stixels_job* jobs, int32_t n, Plan* p) {
     return choose_grid(b, p->slots, p->nch, p->waves, p->pairs, p->stride, p->ntasks, &p->grid);
 }
 
-hipError_t launch(stixels_batch* b, const Plan& p, const JobDesc* jobs, const int2* tasks,
-                  unsigned int* counter, const PoseItem* poses, hipStream_t st) {
+hipError_t launch(stixels_batch* b, const Plan& p, const Block& d, const PoseItem* poses,
+                  hipStream_t st) {
+    const JobDesc* const jobs = d.jobs;
+    const int2* const tasks = d.tasks;
+    unsigned int* const counter = d.counter;
     const hipError_t e = launch_pose_tables(poses, b->npose, b->pose_hmax, st);
     if (e != hipSuccess) return e;
     if (p.chain) {
-        hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, st, counter);
         return launch_chain_batch(jobs, tasks, p.ntasks, counter, b->d_scratch, p.stride, p.hmax,
                                   p.grid, p.waves, st);
     }
@@ -344,19 +353,16 @@ int stixels_batch_create(const stixels_batch_config* cfg, stixels_batch** out) {
             b->scratch_floats = std::max(b->scratch_floats,
                                          (size_t)pgrid * 2 * (size_t)(8 + cfg->max_disparity) *
                                              (size_t)(cfg->max_height + 1));
+        const size_t block = tasks_at(cfg->max_jobs) + sizeof(int2) * (size_t)cfg->max_tasks;
         const bool ok =
-            hipMalloc(reinterpret_cast<void**>(&b->d_jobs), sizeof(JobDesc) * cfg->max_jobs) == hipSuccess &&
-            hipMalloc(reinterpret_cast<void**>(&b->d_tasks), sizeof(int2) * cfg->max_tasks) == hipSuccess &&
-            hipMalloc(reinterpret_cast<void**>(&b->d_counter), sizeof(unsigned int)) == hipSuccess &&
-            hipMalloc(reinterpret_cast<void**>(&b->d_jobs_g), sizeof(JobDesc) * cfg->max_jobs) == hipSuccess &&
-            hipMalloc(reinterpret_cast<void**>(&b->d_tasks_g), sizeof(int2) * cfg->max_tasks) == hipSuccess &&
-            hipMalloc(reinterpret_cast<void**>(&b->d_counter_g), sizeof(unsigned int)) == hipSuccess &&
+            hipMalloc(reinterpret_cast<void**>(&b->d_block), block) == hipSuccess &&
+            hipMalloc(reinterpret_cast<void**>(&b->d_block_g), block) == hipSuccess &&
             hipMalloc(reinterpret_cast<void**>(&b->d_scratch),
                       sizeof(float) * b->scratch_floats + kTableGuardBytes) == hipSuccess &&
-            hipHostMalloc(reinterpret_cast<void**>(&b->h_jobs), sizeof(JobDesc) * cfg->max_jobs, hipHostMallocDefault) == hipSuccess &&
-            hipHostMalloc(reinterpret_cast<void**>(&b->h_tasks), sizeof(int2) * cfg->max_tasks, hipHostMallocDefault) == hipSuccess &&
+            hipHostMalloc(reinterpret_cast<void**>(&b->h_block), block, hipHostMallocDefault) == hipSuccess &&
             hipEventCreateWithFlags(&b->staged, hipEventDisableTiming) == hipSuccess;
         if (!ok) rc = STIXELS_E_NOMEM;
+        else *block_of(b->h_block, 0).counter = 0u;
     }
 #ifdef STX_PHASE_TIMING
     if (rc == STIXELS_OK &&
@@ -389,20 +395,15 @@ int stixels_batch_destroy(stixels_batch* b) {
     if (!b) return STIXELS_OK;
     if (b->staged_pending) (void)hipEventSynchronize(b->staged);
     destroy_graph(b);
-    (void)hipFree(b->d_jobs);
-    (void)hipFree(b->d_tasks);
-    (void)hipFree(b->d_counter);
-    (void)hipFree(b->d_jobs_g);
-    (void)hipFree(b->d_tasks_g);
-    (void)hipFree(b->d_counter_g);
+    (void)hipFree(b->d_block);
+    (void)hipFree(b->d_block_g);
     (void)hipFree(b->d_phase);
     (void)hipFree(b->d_scratch);
     (void)hipFree(b->d_pose_area);
     (void)hipFree(b->d_pose_items);
     (void)hipFree(b->d_pose_items_g);
     if (b->h_pose_items) (void)hipHostFree(b->h_pose_items);
-    if (b->h_jobs) (void)hipHostFree(b->h_jobs);
-    if (b->h_tasks) (void)hipHostFree(b->h_tasks);
+    if (b->h_block) (void)hipHostFree(b->h_block);
     if (b->staged) (void)hipEventDestroy(b->staged);
     delete b;
     return STIXELS_OK;
@@ -414,9 +415,9 @@ int stixels_batch_compute(stixels_batch* b, const stixels_job* jobs, int32_t n, 
     int rc = plan(b, jobs, n, &p);
     if (rc != STIXELS_OK) return rc;
     const hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = upload(b, b->d_jobs, b->d_tasks, b->d_pose_items, n, p.ntasks, st);
+    rc = upload(b, b->d_block, b->d_pose_items, n, p.ntasks, st);
     if (rc != STIXELS_OK) return rc;
-    const hipError_t e = launch(b, p, b->d_jobs, b->d_tasks, b->d_counter, b->d_pose_items, st);
+    const hipError_t e = launch(b, p, block_of(b->d_block, n), b->d_pose_items, st);
     if (e != hipSuccess)
         return bfail(b, STIXELS_E_HIP, std::string("batch launch failed: ") + hipGetErrorString(e));
     remember(b, p);
@@ -432,7 +433,7 @@ int stixels_batch_capture(stixels_batch* b, const stixels_job* jobs, int32_t n, 
     if (rc != STIXELS_OK) return rc;
     const hipStream_t st = static_cast<hipStream_t>(stream);
     // the graph reads its own descriptor copy, uploaded once here
-    rc = upload(b, b->d_jobs_g, b->d_tasks_g, b->d_pose_items_g, n, p.ntasks, st);
+    rc = upload(b, b->d_block_g, b->d_pose_items_g, n, p.ntasks, st);
     if (rc != STIXELS_OK) return rc;
     if (hipStreamSynchronize(st) != hipSuccess)
         return bfail(b, STIXELS_E_HIP, "synchronising the capture stream failed");
@@ -440,8 +441,10 @@ int stixels_batch_capture(stixels_batch* b, const stixels_job* jobs, int32_t n, 
     destroy_graph(b);
     if (hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) != hipSuccess)
         return bfail(b, STIXELS_E_HIP, "hipStreamBeginCapture failed");
-    const hipError_t e =
-        launch(b, p, b->d_jobs_g, b->d_tasks_g, b->d_counter_g, b->d_pose_items_g, st);
+    const Block d = block_of(b->d_block_g, n);
+    // every replay starts with a zero counter
+    hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, st, d.counter);
+    const hipError_t e = launch(b, p, d, b->d_pose_items_g, st);
     hipGraph_t g = nullptr;
     const hipError_t e2 = hipStreamEndCapture(st, &g);
     if (e != hipSuccess || e2 != hipSuccess || !g) {
@@ -491,8 +494,7 @@ int stixels_batch_columns(const stixels_batch* b) { return b ? b->last_columns :
 
 int stixels_batch_device_bytes(const stixels_batch* b, size_t* bytes) {
     if (!b || !bytes) return STIXELS_E_INVALID_ARG;
-    *bytes = 2 * (sizeof(JobDesc) * (size_t)b->cfg.max_jobs +
-                  sizeof(int2) * (size_t)b->cfg.max_tasks + sizeof(unsigned int)) +
+    *bytes = 2 * (tasks_at(b->cfg.max_jobs) + sizeof(int2) * (size_t)b->cfg.max_tasks) +
              sizeof(float) * b->scratch_floats + kTableGuardBytes;
     if (b->d_pose_area)
         *bytes += (b->pose_area_bytes + 2 * sizeof(PoseItem)) * (size_t)b->cfg.max_jobs;
