@@ -240,10 +240,19 @@ class FrameOutput:
     def __init__(self, ncols: int, capacity: int, device):
         import torch
         self.ncols, self.capacity = int(ncols), int(capacity)
-        self.counts = torch.zeros(ncols, dtype=torch.int32, device=device)
-        self.records = torch.zeros((ncols, capacity, 3), dtype=torch.int32, device=device)
-        self.total = torch.zeros(ncols, dtype=torch.float32, device=device)
-        self.overflow = torch.zeros(ncols, dtype=torch.uint8, device=device)
+        # one allocation and one zero fill for the four of them, each at a
+        # multiple of 256 bytes
+        sizes = [12 * self.ncols * self.capacity, 4 * self.ncols, 4 * self.ncols, self.ncols]
+        at, end = [], 0
+        for n in sizes:
+            at.append(end)
+            end += (n + 255) & ~255
+        whole = torch.zeros(end, dtype=torch.uint8, device=device)
+        rec, cnt, tot, ovf = (whole[a:a + n] for a, n in zip(at, sizes))
+        self.counts = cnt.view(torch.int32)
+        self.records = rec.view(torch.int32).view(self.ncols, self.capacity, 3)
+        self.total = tot.view(torch.float32)
+        self.overflow = ovf
 
     def struct(self) -> Output:
         o = Output()

@@ -91,6 +91,13 @@ class GpuExecutor:
         # column, workgroups); untuned classes leave the waves to the library
         # (by rows and columns of each launch) and use the occupancy limit
         self.layout = {}
+        self.num_cu = torch.cuda.get_device_properties(
+            torch.cuda.current_device()).multi_processor_count
+
+    #: columns per compute unit up to which the classes of an admission share
+    #: a launch (the library's own line for spreading the columns of its
+    #: shorter frames over workgroups)
+    SHORT = 9
 
     def layout_for(self, k: int):
         return self.layout.get(k, (1, 0, 0))
@@ -128,23 +135,48 @@ class GpuExecutor:
     def slots(self) -> int:
         return len(self.free)
 
+    def grouped(self, reqs):
+        """The launches of an admission: (height class, its requests), tallest
+        class first.  A class joins the launch of the next taller one while
+        both leave their layout to the library and the columns together are at
+        most SHORT per compute unit: a launch that short spreads each column
+        over a workgroup whatever its height, and two such launches in a row
+        leave the chip partly idle twice (two frames 1024x440 and one 1280x720:
+        80 and 103 us one after the other)."""
+        groups = {}
+        for r in reqs:
+            groups.setdefault(self.cameras[r.camera].height_class(), []).append(r)
+        launches = []
+        for k in sorted(groups, reverse=True):
+            if launches:
+                top, members = launches[-1]
+                hmax, dmax, cols = self.classes[top]
+                both = members + groups[k]
+                ncols = sum(self.cameras[r.camera].ncols() for r in both)
+                if (self.layout_for(top) == self.layout_for(k) == (1, 0, 0)
+                        and len(both) <= self.max_frames
+                        and ncols <= min(self.SHORT * self.num_cu, self.max_frames * cols)
+                        and max(self.cameras[r.camera].handle.D for r in groups[k]) <= dmax):
+                    launches[-1] = (top, both)
+                    continue
+            launches.append((k, groups[k]))
+        return launches
+
     def launch(self, reqs):
         """Allocate the requests' outputs and enqueue the batched launches,
         all on one stream (the allocation's zero fill is stream-ordered before
         the kernels that write the results).  Frames are grouped by height
         class, one launch per class, so short frames never run the
-        register-heavy variant sized for tall ones."""
+        register-heavy variant sized for tall ones; where the library picks
+        the layout and the launch is short, the classes share one (grouped)."""
         i = self.free.pop()
         st = self.streams[i]
         with self._torch.cuda.stream(st):
             for r in reqs:
                 c = self.cameras[r.camera]
                 r.out = c.handle.new_output(c.width, c.height)
-        groups = {}
-        for r in reqs:
-            groups.setdefault(self.cameras[r.camera].height_class(), []).append(r)
-        for k in sorted(groups, reverse=True):
-            items = [(self.cameras[r.camera].handle, r.frame, r.out) for r in groups[k]]
+        for k, members in self.grouped(reqs):
+            items = [(self.cameras[r.camera].handle, r.frame, r.out) for r in members]
             b = self.batches[i][k]
             cols, waves, wg = self.layout_for(k)
             b.set_columns(cols)
