@@ -133,11 +133,11 @@ __attribute__((amdgpu_waves_per_eu(batch_waves((S + W - 1) / W, W)))) void batch
     __shared__ int band_lo[S], band_hi[S], band_base[S], band_all[3];
     __shared__ int task_slot;
     __shared__ int red[3][W];
-    // one-wave banded columns of up to 8 slots: rcp(2 n) for n = 0 .. 64 S,
-    // read by the recurrence in place of a v_rcp_f32 per candidate (the same
+    // one-wave banded columns of up to 8 slots, and tall ones of several
+    // waves: rcp(2 n) for n = 0 .. 64 S, read by the recurrence in place of a v_rcp_f32 per candidate (the same
     // values; rcp(0) = +inf); written once per workgroup, before the first
     // task's barriers
-    constexpr bool RT = BAND && W == 1 && S <= 8;
+    constexpr bool RT = BAND && ((W == 1 && S <= 8) || (S > 8 && (S + W - 1) / W <= 8));
     __shared__ float rtab[RT ? 64 * S + 1 : 1];
     const int lane = threadIdx.x & 63;
     const int wave = (W == 1) ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));

@@ -518,6 +518,7 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
                              const float* po_lds = nullptr) {
     static_assert(W == 1 || W == 2 || W == 4, "waves per column");
     constexpr int SW = (S + W - 1) / W;              // slots per wave
+    constexpr bool TALL = BAND && S > 8 && SW <= 8;
     const int lane = threadIdx.x & 63;
     const int wave = (W == 1) ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int stride = H + 1;
@@ -636,19 +637,31 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
     // sky and ground prefixes and the ground-disparity bounds of the next
     // step are prefetched with it.  All go through buffer resources: unlike
     // flat loads they do not hold up the waits on this step's LDS traffic.
-    // A base's stixels hold no pixel below it, so the second chunk's means are
-    // out of their reach past the last row jtwo with a pixel in that chunk, and
-    // from there its part of the table, of the object column and of the cost
-    // rows is left out (disparities fall with the row: most steps of a road
-    // scene.  64 frames 1024x440, one wave per column: 1,160 -> 1,117 us, a
-    // tenth fewer vector instructions.  Four chunks keep theirs: a test per
-    // chunk and step cost what it saved, 16 frames 2048x880 6,187 -> 6,261).
-    int jtwo = -1;
-    if constexpr (NCH == 2) {
-        for (int v = lane; v < H; v += 64) jtwo = ((int)in.q[v] - fbase >= 64) ? v : jtwo;
+    // A base's stixels hold no pixel below it, so the means of a chunk are out
+    // of their reach past the last row jlast[c] with a pixel of that chunk or a
+    // larger one, and from there its part of the prior table is left out
+    // (disparities fall with the row: most steps of a road scene), with two
+    // chunks also its part of the object column and of the cost rows.  64 frames
+    // 1024x440, one wave per column: 1,160 -> 1,117 us, a tenth fewer vector
+    // instructions.  Four chunks, 16 frames 2048x880, two waves: 5,440 -> 5,230
+    // us; leaving out the column and the cost rows as well 5,500 (a branch each).
+    constexpr bool TABLE4 = TALL && NCH > 2;
+    int jlast[NCH];
+    jlast[0] = H;
+    if constexpr (NCH == 2 || TABLE4) {
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) jtwo = max(jtwo, __shfl_xor(jtwo, o, 64));
-        jtwo = __builtin_amdgcn_readfirstlane(jtwo);
+        for (int c = 1; c < NCH; ++c) jlast[c] = -1;
+        for (int v = lane; v < H; v += 64) {
+            const int q = (int)in.q[v] - fbase;
+#pragma unroll
+            for (int c = 1; c < NCH; ++c) jlast[c] = (q >= 64 * c) ? v : jlast[c];
+        }
+#pragma unroll
+        for (int c = 1; c < NCH; ++c) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) jlast[c] = max(jlast[c], __shfl_xor(jlast[c], o, 64));
+            jlast[c] = __builtin_amdgcn_readfirstlane(jlast[c]);
+        }
     }
     float pcol[NCH], orow[NCH];
     int thi_n = 0, tlo_n = 0;
@@ -674,15 +687,21 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
     // BLOCKS these four are prefetched a step ahead).  A step takes its own
     // with readlane (scalar registers); with BLOCKS only the object gathers
     // and the object-cost row are vector memory instructions of a step.
-    constexpr bool QB = (S <= 8);                    // the pixel a slot at a time
+    // Tall columns shared by two or four waves do all of this, and PIPE, where
+    // the table is banded (TALL): their steps waited for the gathers, each wave
+    // twice over.  16 frames 2048x880, 3-pixel columns, two waves 6,760 -> 4,840
+    // us; 8 frames, 5-pixel columns, four waves 3,980 -> 2,920; 16 frames
+    // 1280x720, two waves 2,090 -> 1,585 (with three waves per SIMD instead of
+    // four, and no spills, the first took 6,150 where it took 5,440 with four).
+    constexpr bool QB = (S <= 8) || TALL;            // the pixel a slot at a time
     constexpr bool BLK = BLOCKS && QB;               // and the other four
-    // PIPE: one-wave columns of up to 8 slots gather a step's object
-    // prefixes one step early.  The gathers of step j (stixels starting at
+    // PIPE: one-wave columns of up to 8 slots, and TALL ones, gather a step's
+    // object prefixes one step early.  The gathers of step j (stixels starting at
     // b = j+1) depend only on row j's prefix values, never on a cost, so
     // step j issues them for step j+1 right after folding its own, and a
     // whole step of work covers their latency.  The slot also holds the
     // prefix values of row j+1 of each of its steps.
-    constexpr bool PIPE = (W == 1) && QB;
+    constexpr bool PIPE = (W == 1 && S <= 8) || TALL;
     struct Blk {
         int q = 0, thi = 0, tlo = 0;
         float ps = 0.0f, pg = 0.0f;
@@ -747,8 +766,12 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
     float pkP[PIPE ? SW : 1];
     int fSP[PIPE ? SW : 1];
     if constexpr (PIPE) {
-        const float nA0 = readlane_f(eA[0], 0);
-        const NT nN0 = readlane_n(eN[0], 0);
+        // slot 0 belongs to wave 0: the others read the tables
+        const float nA0 = (W == 1) ? readlane_f(eA[0], 0) : in.PA[1];
+        NT nN0;
+        if constexpr (W == 1) nN0 = readlane_n(eN[0], 0);
+        else if constexpr (RT) nN0 = (int)in.PN2[1] * 2;
+        else nN0 = in.PN2[1];
 #pragma unroll
         for (int t = 0; t < SW; ++t) {
             if constexpr (BAND) {
@@ -786,10 +809,12 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
     // constant at every call, so that row j's registers are read by one
     // readlane each (a run-time slot would read every slot and select)
     // two_tag: whether the second of two chunks is still needed (NCH = 2)
-    auto step = [&](auto gr_tag, auto two_tag, const int sj, const int jl, const int tj,
+    // lim_tag: the wave's slots that may hold rows of this column (TALL)
+    auto step = [&](auto gr_tag, auto two_tag, auto lim_tag, const int sj, const int jl, const int tj,
                     const Blk& blk) {
         constexpr bool GR = decltype(gr_tag)::value;
         constexpr bool TWO = decltype(two_tag)::value;
+        constexpr int LIM = decltype(lim_tag)::value;
         const int j = sj * 64 + jl, b = j + 1;
         // row j's object cost, mean and prefix values, read from its owning
         // lane; the slot is chosen by wave-uniform branches (an indexed
@@ -952,8 +977,8 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
         if constexpr (PIPE && RT) {
             const NT nN = readlane_n(blk.nn, jl);
 #pragma unroll
-            for (int t = 0; t < SW; ++t) {
-                if (t < sj) continue;
+            for (int t = 0; t < LIM; ++t) {
+                if (t < tj) continue;
                 rP[t] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(rtab) +
                                                         (eN[t] - nN));
             }
@@ -964,7 +989,7 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
         for (int c = 0; c < NCH; ++c) {
             // two chunks are built in one block, so that their compares and
             // selects interleave
-            if (NCH <= 2 ? (c == 1 && !TWO) : (c >= nchunk)) break;
+            if (NCH <= 2 ? (c == 1 && !TWO) : (TABLE4 ? j >= jlast[c] : c >= nchunk)) break;
             const int f = fbase + 64 * c + lane;
             const float v1 = (f > tord) ? Xoo_p : Xoo;
             float pr;
@@ -984,10 +1009,15 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
             // with this step still gathers once, into rows never folded
             const float nA = readlane_f(blk.na, jl);
             const NT nN = readlane_n(blk.nn, jl);
+            auto open = [&](int t) {
+                if constexpr (W == 1) return (t > tj) || (lane > jl);
+                const int s = t * W + wave;
+                return (s > sj) || (s == sj && lane > jl);
+            };
             float qv[SW];
 #pragma unroll
-            for (int t = 0; t < SW; ++t) {
-                if (t < sj) continue;
+            for (int t = 0; t < LIM; ++t) {
+                if (t < tj) continue;
                 if constexpr (BAND) {
                     // byte offset (mean - fbase) * 4 >= -4: the table's padding
                     qv[t] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(qtab) + fSP[t]);
@@ -996,9 +1026,9 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
                 }
             }
 #pragma unroll
-            for (int t = 0; t < SW; ++t) {
-                if (t < sj) continue;
-                const bool act = (t > sj) || (lane > jl);          // rows k > j only
+            for (int t = 0; t < LIM; ++t) {
+                if (t < tj) continue;
+                const bool act = open(t);                          // rows k > j only
                 float cO = qv[t] + pkP[t];
                 cO = act ? cO : INF;
                 const bool better = cO < mO[t];
@@ -1034,9 +1064,9 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
                         pr0 = vmin(v1, Xso);
                     }
 #pragma unroll
-                    for (int t = 0; t < SW; ++t) {
-                        if (t < sj) continue;
-                        const bool act = ((t > sj) || (lane > jl)) && (eN[t] == nN);
+                    for (int t = 0; t < LIM; ++t) {
+                        if (t < tj) continue;
+                        const bool act = open(t) && (eN[t] == nN);
                         const bool better = act && (pr0 < mO[t]);
                         mO[t] = better ? pr0 : mO[t];
                         fO[t] = better ? 0 : fO[t];
@@ -1108,6 +1138,7 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
         }
     };
 
+    using All = std::integral_constant<int, SW>;
     if constexpr (S <= 8) {
         // unrolled over the slot of row j, so that every slot test above is
         // decided at compile time (for W = 1) and the slots' gathers share
@@ -1124,49 +1155,59 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
             __builtin_amdgcn_s_waitcnt(0);
             // steps whose base b = sj*64+jl+1 can still follow a ground stixel
             const int jgr = min(jend, max(0, vtop + 1 - sj * 64));
-            // and those that may reach the second chunk's means
-            const int jtw = min(jend, jtwo - sj * 64);
             int jl = 0;
             if constexpr (NCH == 2) {
+                // those that may reach the second chunk's means
+                const int jtw = min(jend, jlast[1] - sj * 64);
                 for (; jl < min(jgr, jtw); ++jl)
-                    step(std::true_type{}, std::true_type{}, sj, jl, sj / W, blk);
+                    step(std::true_type{}, std::true_type{}, All{}, sj, jl, sj / W, blk);
                 for (; jl < jtw; ++jl)
-                    step(std::false_type{}, std::true_type{}, sj, jl, sj / W, blk);
+                    step(std::false_type{}, std::true_type{}, All{}, sj, jl, sj / W, blk);
             }
-            for (; jl < jgr; ++jl) step(std::true_type{}, std::false_type{}, sj, jl, sj / W, blk);
-            for (; jl < jend; ++jl) step(std::false_type{}, std::false_type{}, sj, jl, sj / W, blk);
+            for (; jl < jgr; ++jl) step(std::true_type{}, std::false_type{}, All{}, sj, jl, sj / W, blk);
+            for (; jl < jend; ++jl) step(std::false_type{}, std::false_type{}, All{}, sj, jl, sj / W, blk);
         }
     } else if constexpr (SW <= 8) {
         // tall columns shared by several waves: one copy of the step per
         // local slot of row j's owner (at most 8, as for short columns),
         // the owning wave a run-time loop
-        const Blk none;
-        static_for<0, SW>([&](auto tc) {
-            constexpr int T = decltype(tc)::value;
-            for (int wj = 0; wj < W; ++wj) {
-                const int sj = T * W + wj;
-                const int jend = min(64, H - 1 - sj * 64);
-                if (jend <= 0) break;
-                const int jgr = min(jend, max(0, vtop + 1 - sj * 64));
-                const int jtw = min(jend, jtwo - sj * 64);
-                int jl = 0;
-                if constexpr (NCH == 2) {
-                    for (; jl < min(jgr, jtw); ++jl)
-                        step(std::true_type{}, std::true_type{}, sj, jl, T, none);
-                    for (; jl < jtw; ++jl)
-                        step(std::false_type{}, std::true_type{}, sj, jl, T, none);
+        auto rows = [&](auto lim) {
+            static_for<0, decltype(lim)::value>([&](auto tc) {
+                constexpr int T = decltype(tc)::value;
+                for (int wj = 0; wj < W; ++wj) {
+                    const int sj = T * W + wj;
+                    const int jend = min(64, H - 1 - sj * 64);
+                    if (jend <= 0) break;
+                    Blk blk;
+                    if constexpr (QB) {
+                        blk = load_block(sj);
+                        __builtin_amdgcn_s_waitcnt(0);          // as above
+                    }
+                    const int jgr = min(jend, max(0, vtop + 1 - sj * 64));
+                    int jl = 0;
+                    if constexpr (NCH == 2) {
+                        const int jtw = min(jend, jlast[1] - sj * 64);
+                        for (; jl < min(jgr, jtw); ++jl)
+                            step(std::true_type{}, std::true_type{}, lim, sj, jl, T, blk);
+                        for (; jl < jtw; ++jl)
+                            step(std::false_type{}, std::true_type{}, lim, sj, jl, T, blk);
+                    }
+                    for (; jl < jgr; ++jl) step(std::true_type{}, std::false_type{}, lim, sj, jl, T, blk);
+                    for (; jl < jend; ++jl) step(std::false_type{}, std::false_type{}, lim, sj, jl, T, blk);
                 }
-                for (; jl < jgr; ++jl) step(std::true_type{}, std::false_type{}, sj, jl, T, none);
-                for (; jl < jend; ++jl) step(std::false_type{}, std::false_type{}, sj, jl, T, none);
-            }
-        });
+            });
+        };
+        // a shorter frame's column in a launch sized for tall ones: half the slots
+        constexpr int HALF = TALL ? (SW + 1) / 2 : SW;
+        if (HALF < SW && nslots <= HALF * W) rows(std::integral_constant<int, HALF>{});
+        else rows(All{});
     } else {
         // tall one-wave columns: one runtime loop keeps the code (and the
         // registers live across it) to a single copy of the step
         const Blk none;
         for (int j = 0; j < H - 1; ++j) {
-            if (j + 1 <= vtop + 1) step(std::true_type{}, std::true_type{}, j >> 6, j & 63, (j >> 6) / W, none);
-            else step(std::false_type{}, std::true_type{}, j >> 6, j & 63, (j >> 6) / W, none);
+            if (j + 1 <= vtop + 1) step(std::true_type{}, std::true_type{}, All{}, j >> 6, j & 63, (j >> 6) / W, none);
+            else step(std::false_type{}, std::true_type{}, All{}, j >> 6, j & 63, (j >> 6) / W, none);
         }
     }
 
