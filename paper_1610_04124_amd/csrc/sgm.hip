@@ -649,18 +649,20 @@ int stixels_sgm_create(const stixels_sgm_params* params, stixels_sgm** out) {
     if (hipDeviceGetAttribute(&m->ws.num_cu, hipDeviceAttributeMultiprocessorCount, m->device) !=
         hipSuccess)
         m->ws.num_cu = 0;
-    const size_t planes =
-        nd * (stx::sgm::packed_four(p.max_disparity, p.max_height, p.max_frames, m->ws.num_cu) ? 4 : 3);
-    if (ok && stx::sgm::packed_costs(p.p2) &&
-        hipMalloc(reinterpret_cast<void**>(&m->ws.planes), planes) == hipSuccess) {
-        m->ws.plane_bytes = planes;
-        m->bytes += planes;
-    } else if (ok) {
-        (void)hipGetLastError();
-        m->ws.planes = nullptr;
+    const bool four =
+        stx::sgm::packed_four(p.max_disparity, p.max_height, p.max_frames, m->ws.num_cu);
+    if (ok && stx::sgm::packed_costs(p.p2))
+        for (size_t n = four ? 4 : 3; n >= 3 && !m->ws.planes; --n) {
+            if (hipMalloc(reinterpret_cast<void**>(&m->ws.planes), n * nd) == hipSuccess) {
+                m->ws.plane_bytes = n * nd;
+            } else {
+                (void)hipGetLastError();
+                m->ws.planes = nullptr;
+            }
+        }
+    if (ok && !m->ws.planes)
         ok = hipMalloc(reinterpret_cast<void**>(&m->ws.S), nd * sizeof(uint16_t)) == hipSuccess;
-        m->bytes += nd * sizeof(uint16_t);
-    }
+    m->bytes += m->ws.planes ? m->ws.plane_bytes : nd * sizeof(uint16_t);
     if (!ok) {
         (void)hipFree(m->ws.cl);
         (void)hipFree(m->ws.cr);

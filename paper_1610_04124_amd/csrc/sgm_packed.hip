@@ -18,11 +18,11 @@
 //     t = C + min(L, sat(min(L(d-1), L(d+1)) + P1), P2),  L = t - min over d of t
 // (t is the path cost).  With eight disparities to a lane and 16 lanes to a line
 // that is 82 instructions for 512 disparities (95 us of a pair against 212):
-// 32 + 4 of them the Hamming costs, 8 the minimum over the line, which four
+// 32 + 4 of them the Hamming costs, 6 the minimum over the line, which four
 // disparities to a lane pay for 256.  With few lines the chain of a row's steps
-// bounds it, and a line is spread over a wave instead (41 instructions a step).
+// bounds it, and the Hamming costs go to a second wave (row_pair_pass).
 // 1024x440, 128 disparities, before (one disparity per register, four launches
-// over 16-bit sums) and now: one pair 894 / 216 us, 64 pairs 13.56 / 6.06 ms,
+// over 16-bit sums) and now: one pair 888 / 190 us, 64 pairs 13.56 / 6.03 ms,
 // of these 3.5 the three directions (11 GB written), 2.2 the last one and the
 // selection (11 GB read, 5 TB/s), 0.4 the census.
 #include <hip/hip_runtime.h>
@@ -426,8 +426,8 @@ struct RowWords {
     }
 };
 
-// Row lines whose costs go to memory: block of G waves, 64 / LPL rows each.
-template <int LPL, int R, int G, bool RIGHT>
+// Right-to-left rows where lines are many: block of G waves, 64 / LPL rows each.
+template <int LPL, int R, int G>
 __device__ __forceinline__ void row_pass(const PackedArgs& a, const int block, uint8_t* plane) {
     constexpr int Dpad = 2 * R * LPL, LPW = 64 / LPL;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -439,11 +439,11 @@ __device__ __forceinline__ void row_pass(const PackedArgs& a, const int block, u
     Line<LPL, R> ln;
     ln.init(lane, D);
     // uniform address and the lane's offset from it
-    uint8_t* out = plane + ((size_t)first * W + (RIGHT ? 0 : W - 1)) * (size_t)D;
+    uint8_t* out = plane + ((size_t)first * W + W - 1) * (size_t)D;
     const uint32_t off = ln.d0 < D && first + lane / LPL < lines
                              ? (uint32_t)((line - first) * W * D + ln.d0) : kNowhere;
     const uint32_t P1 = (uint32_t)a.P1 * 0x10001u, P2 = (uint32_t)a.P2 * 0x10001u;
-    RowWords<LPL, R, RIGHT> rw;
+    RowWords<LPL, R, false> rw;
     rw.init(a, ro, lane, ln.d0);
     auto steps = [&](auto INSIDE, int s0) {
         unrolled<kTurn>([&](auto U) {
@@ -451,12 +451,12 @@ __device__ __forceinline__ void row_pass(const PackedArgs& a, const int block, u
             const int s = s0 + u;
             uint32_t C[R], t[R];
             ln.template cost<decltype(INSIDE)::value>(row_word<u>(rw.left), rw.w,
-                                                      RIGHT ? s : W - 1 - s, C);
+                                                      W - 1 - s, C);
             ln.step(C, P1, P2, t);
             Bytes<R> b;
             b.pack(t);
             b.store(out, decltype(INSIDE)::value || s < W ? off : kNowhere);
-            out = RIGHT ? out + D : out - D;
+            out -= D;
             rw.template slide<u>(ln);
         });
     };
@@ -464,12 +464,7 @@ __device__ __forceinline__ void row_pass(const PackedArgs& a, const int block, u
     // loops of their own: as the sides of a branch in one loop, each side's
     // state would live through the other's
     int s0 = 0;
-    if (RIGHT)
-        for (; s0 < min(W, Dpad - 1); s0 += kTurn) {
-            rw.turn(s0);
-            steps(std::false_type{}, s0);
-        }
-    for (; RIGHT ? s0 + kTurn <= W : W - kTurn - s0 >= Dpad - 1; s0 += kTurn) {
+    for (; W - kTurn - s0 >= Dpad - 1; s0 += kTurn) {
         rw.turn(s0);
         steps(std::true_type{}, s0);
     }
@@ -479,28 +474,121 @@ __device__ __forceinline__ void row_pass(const PackedArgs& a, const int block, u
     }
 }
 
+// Rows where lines are few: a pair of waves per row, one that forms the Hamming
+// costs kTurn steps ahead (double-buffered in LDS), one that runs the
+// recurrence over them, whose chain bounds the call.  Against a wave that does
+// both, a row spread over all its 64 lanes (two disparities each): 1024x440 and
+// 128 disparities 218 -> 190 us at one pair, 699 -> 616 at four; 641x241 and 64
+// 115 -> 85 at one.  (Columns in such pairs as well: 214 and 640.)
+template <int R, int G>
+struct PairStage {
+    uint32_t c[G / 2][2][kTurn * R * 64];
+};
+
+template <int LPL, int R, int G, bool RIGHT>
+__device__ __forceinline__ void row_pair_pass(const PackedArgs& a, PairStage<R, G>& stage,
+                                              const int block, uint8_t* plane) {
+    constexpr int Dpad = 2 * R * LPL, LPW = 64 / LPL;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int W = a.W, D = a.D, lines = a.H * a.frames;
+    // the roles change places from block to block, so that neighbours on a
+    // compute unit don't put their chains on the same SIMDs
+    const int role = ((wave & 1) ^ (block & 1)), pair = wave >> 1;
+    const int first = min((block * (G / 2) + pair) * LPW, lines - 1);
+    const int line = min(first + lane / LPL, lines - 1);
+    const bool real = (block * (G / 2) + pair) * LPW + lane / LPL < lines;
+    const size_t ro = (size_t)line * W;
+    Line<LPL, R> ln;
+    ln.init(lane, D);
+    const int turns = (W + kTurn - 1) / kTurn;
+    uint32_t* const mine = &stage.c[pair][0][lane];
+    if (role == 0) {
+        RowWords<LPL, R, RIGHT> rw;
+        rw.init(a, ro, lane, ln.d0);
+        auto turn = [&](auto INSIDE, int t) {
+            const int s0 = t * kTurn;
+            rw.turn(s0);
+            uint32_t* const to = mine + (t & 1) * kTurn * R * 64;
+            unrolled<kTurn>([&](auto U) {
+                constexpr int u = decltype(U)::value;
+                uint32_t C[R];
+                const int s = s0 + u;
+                ln.template cost<decltype(INSIDE)::value>(row_word<u>(rw.left), rw.w,
+                                                          RIGHT ? s : W - 1 - s, C);
+#pragma unroll
+                for (int r = 0; r < R; ++r) to[(u * R + r) * 64] = C[r];
+                rw.template slide<u>(ln);
+            });
+            lds_barrier();
+        };
+        int t = 0;
+        if (RIGHT)
+            for (; t < turns && t * kTurn < Dpad - 1; ++t) turn(std::false_type{}, t);
+        for (; RIGHT ? t < turns : (t < turns && W - kTurn - t * kTurn >= Dpad - 1); ++t)
+            turn(std::true_type{}, t);
+        for (; t < turns; ++t) turn(std::false_type{}, t);
+    } else {
+        // uniform address and the lane's offset from it
+        uint8_t* out = plane + ((size_t)first * W + (RIGHT ? 0 : W - 1)) * (size_t)D;
+        const uint32_t off =
+            ln.d0 < D && real ? (uint32_t)((line - first) * W * D + ln.d0) : kNowhere;
+        const uint32_t P1 = (uint32_t)a.P1 * 0x10001u, P2 = (uint32_t)a.P2 * 0x10001u;
+        auto turn = [&](auto FULL, int t) {
+            lds_barrier();
+            const uint32_t* const from = mine + (t & 1) * kTurn * R * 64;
+            uint32_t C[kTurn][R];
+#pragma unroll
+            for (int u = 0; u < kTurn; ++u)
+#pragma unroll
+                for (int r = 0; r < R; ++r) C[u][r] = from[(u * R + r) * 64];
+#pragma unroll
+            for (int u = 0; u < kTurn; ++u) {
+                uint32_t c[R];
+                ln.step(C[u], P1, P2, c);
+                Bytes<R> b;
+                b.pack(c);
+                b.store(out, decltype(FULL)::value || t * kTurn + u < W ? off : kNowhere);
+                out = RIGHT ? out + D : out - D;
+            }
+        };
+        for (int t = 0; t < turns - 1; ++t) turn(std::true_type{}, t);
+        turn(std::false_type{}, turns - 1);
+    }
+}
+
 // The directions whose costs go to memory, as ranges of blocks; the rows'
 // lines are the longest, so their blocks go first.
-template <int LPL_R, int R_R, int LPL_C, int R_C, int G, bool FOUR>
+template <int LPL, int R, int G, bool FOUR>
 __global__ __launch_bounds__(64 * G) void paths_kernel(PackedArgs a, int row_blocks, int col_blocks) {
-    __shared__ ColumnStage<LPL_C, R_C, G> stage;
+    using Columns = ColumnStage<LPL, R, G>;
+    using Rows = PairStage<R, G>;
+    constexpr size_t kShared = !FOUR || sizeof(Columns) > sizeof(Rows) ? sizeof(Columns) : sizeof(Rows);
+    __shared__ __attribute__((aligned(16))) char shared[kShared];
+    Columns& stage = *reinterpret_cast<Columns*>(shared);
     int b = (int)blockIdx.x;
-    if (b < row_blocks) {
-        row_pass<LPL_R, R_R, G, false>(a, xcd_contiguous(b, row_blocks), a.L + 2 * a.plane);
-        return;
-    }
-    b -= row_blocks;
     if constexpr (FOUR) {
+        Rows& pairs = *reinterpret_cast<Rows*>(shared);
+        if (b < 2 * row_blocks) {
+            // a row's two directions next to each other
+            const int r = xcd_contiguous(b, 2 * row_blocks);
+            if (r & 1)
+                row_pair_pass<LPL, R, G, true>(a, pairs, r >> 1, a.L + 3 * a.plane);
+            else
+                row_pair_pass<LPL, R, G, false>(a, pairs, r >> 1, a.L + 2 * a.plane);
+            return;
+        }
+        b -= 2 * row_blocks;
+    } else {
         if (b < row_blocks) {
-            row_pass<LPL_R, R_R, G, true>(a, xcd_contiguous(b, row_blocks), a.L + 3 * a.plane);
+            row_pass<LPL, R, G>(a, xcd_contiguous(b, row_blocks), a.L + 2 * a.plane);
             return;
         }
         b -= row_blocks;
     }
     if (b < col_blocks)
-        column_pass<LPL_C, R_C, G, false>(a, stage, xcd_contiguous(b, col_blocks), a.L);
+        column_pass<LPL, R, G, false>(a, stage, xcd_contiguous(b, col_blocks), a.L);
     else
-        column_pass<LPL_C, R_C, G, true>(a, stage, xcd_contiguous(b - col_blocks, col_blocks),
+        column_pass<LPL, R, G, true>(a, stage, xcd_contiguous(b - col_blocks, col_blocks),
                                          a.L + a.plane);
 }
 
@@ -723,7 +811,7 @@ hipError_t launch_many(const PackedArgs& a, hipStream_t st) {
     const int col = a.frames * ((a.W + G * LPW - 1) / (G * LPW));
     const int lines = a.H * a.frames;
     const int row = (lines + G * LPW - 1) / (G * LPW);
-    hipLaunchKernelGGL((paths_kernel<LPL, R, LPL, R, G, false>), dim3((unsigned)(row + 2 * col)),
+    hipLaunchKernelGGL((paths_kernel<LPL, R, G, false>), dim3((unsigned)(row + 2 * col)),
                        dim3(64 * G), 0, st, a, row, col);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -733,15 +821,14 @@ hipError_t launch_many(const PackedArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Few lines: rows spread over more lanes (LPL_R, R_R), all four directions
-// at once.
-template <int LPL_R, int R_R, int LPL, int R>
+// Few lines: a pair of waves per rows, all four directions at once.
+template <int LPL, int R>
 hipError_t launch_few(const PackedArgs& a, hipStream_t st) {
-    constexpr int G = 4, LPW = 64 / LPL, LPW_R = 64 / LPL_R;
+    constexpr int G = 4, LPW = 64 / LPL;
     const int col = a.frames * ((a.W + G * LPW - 1) / (G * LPW));
     const int lines = a.H * a.frames;
-    const int row = (lines + G * LPW_R - 1) / (G * LPW_R);
-    hipLaunchKernelGGL((paths_kernel<LPL_R, R_R, LPL, R, G, true>), dim3((unsigned)(2 * (row + col))),
+    const int row = (lines + G / 2 * LPW - 1) / (G / 2 * LPW);
+    hipLaunchKernelGGL((paths_kernel<LPL, R, G, true>), dim3((unsigned)(2 * (row + col))),
                        dim3(64 * G), 0, st, a, row, col);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -754,15 +841,15 @@ hipError_t launch_few(const PackedArgs& a, hipStream_t st) {
 
 bool packed_costs(int P2) { return kCostOut + P2 <= 255; }
 
-// Few lines are all four directions side by side: while the waves of one
-// direction's rows (a line over 64, 32 or 16 lanes) are at most 7 per CU.  On
-// 256 CUs, us with few / many lines' kernels: 1024x440 and 128 disparities 360 /
-// 707 at two pairs, 703 / 839 at four, 985 / 884 at six; 2048x880 and 256: 1197
-// / 1745 at one, 2186 / 2500 at two, 3280 / 2875 at three; 641x241 and 64: 140 /
-// 295 at four, 518 / 515 at 16; 640x240 and 32: 282 / 348 at 16, 565 / 533 at 32.
+// Few lines are all four directions side by side: while a compute unit has at
+// most 17 rows of 64 disparities, 14 of 128 or 8 of 256.  On 256 of them, us with
+// few / many lines' kernels: 640x240 and 32 disparities 289 / 347 at 16 pairs,
+// 581 / 538 at 32; 641x241 and 64: 469 / 518 at 16, 707 / 600 at 24; 1024x440 and
+// 128: 617 / 839 at four, 1,081 / 1,219 at eight, 1,589 / 1,420 at twelve;
+// 2048x880 and 256: 1,170 / 1,748 at one, 2,115 / 2,518 at two, 3,163 / 2,913 at
+// three.
 bool packed_four(int D, int H, int frames, int num_cu) {
-    const int lines = D <= 32 ? 4 : (D <= 64 ? 2 : 1);            // of a wave
-    return ((int64_t)H * frames + lines - 1) / lines <= 7 * (int64_t)num_cu;
+    return (int64_t)H * frames <= (int64_t)num_cu * (D <= 64 ? 17 : (D <= 128 ? 14 : 8));
 }
 
 hipError_t launch_packed_paths(const uint64_t* cl, const uint64_t* cr, uint8_t* planes,
@@ -771,11 +858,10 @@ hipError_t launch_packed_paths(const uint64_t* cl, const uint64_t* cr, uint8_t* 
     const PackedArgs a{cl, cr, planes, plane, disp, W, H, D, P1, P2, frames};
     const bool eights = D % 8 == 0;                   // lanes of eight disparities end at D
     if (four) {
-        if (D <= 32) return launch_few<16, 1, 16, 1>(a, st);
-        if (D <= 64) return launch_few<32, 1, 16, 2>(a, st);
-        if (D <= 128)
-            return eights ? launch_few<64, 1, 16, 4>(a, st) : launch_few<64, 1, 32, 2>(a, st);
-        return eights ? launch_few<64, 2, 32, 4>(a, st) : launch_few<64, 2, 64, 2>(a, st);
+        if (D <= 32) return launch_few<16, 1>(a, st);
+        if (D <= 64) return launch_few<16, 2>(a, st);
+        if (D <= 128) return eights ? launch_few<16, 4>(a, st) : launch_few<32, 2>(a, st);
+        return eights ? launch_few<32, 4>(a, st) : launch_few<64, 2>(a, st);
     }
     // four rows' selection state within 64 KB of LDS: fewer rows to a wave past
     // 4096 columns

@@ -46,8 +46,8 @@ def check(m, left, right, D, p1=10, p2=120):
     (4203, 3, 32), (4100, 5, 64), (4099, 2, 128)])
 @pytest.mark.parametrize("many", [False, True])
 def test_layouts_equal_oracle(W, H, D, many):
-    # rows of one direction at most 7 waves per CU are few; a wave holds 4, 2 or 1
-    lines = 7 * 256 * (4 if D <= 32 else 2 if D <= 64 else 1)
+    # at most 17, 14 or 8 rows per compute unit are few
+    lines = 256 * (17 if D <= 64 else 14 if D <= 128 else 8)
     n = lines // H + 2 if many else 3
     left, right = images(np.random.default_rng(W * D + H), 4, H, W)
     left, right = (np.tile(a, (n // 4 + 1, 1, 1))[:n] for a in (left, right))
