@@ -322,10 +322,10 @@ def uneven(warmup, steps, tune_launch=True):
 def sgm_bytes_per_frame(W=W, H=H, D=D_RANGE):
     """Algorithmic HBM bytes of the matching stage per frame: census (both
     images read, both word arrays written), each of the four path passes
-    reading both word arrays once, the summed costs written (first pass),
-    read and written (two passes) and read (last pass), the map written."""
+    reading both word arrays once, three planes of path costs in bytes written
+    and read back by the last pass, the map written."""
     n = W * H
-    return 2 * n + 16 * n + 4 * 16 * n + 2 * n * D * (1 + 2 + 2 + 1) + 4 * n
+    return 2 * n + 16 * n + 4 * 16 * n + n * D * (3 + 3) + 4 * n
 
 
 def stereo(warmup, steps, tune_launch=True):

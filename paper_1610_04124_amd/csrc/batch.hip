@@ -111,13 +111,16 @@ int batch_waves_for(const stixels_batch* b, int slots) {
 // always: the wave's recurrence then runs a loop over slots that it cannot
 // unroll (8 frames 2048x880, 3,272 columns: 1,224 us against 4,992, or 3,172
 // with two waves a column; 32 frames 1280x720, 8,192 columns: 1,952 against
-// 3,766).  Below, while the launch is short: a wave per column takes as long
-// as its chain of steps however few the columns are, but costs less once every
-// SIMD has its waves.  Measured crossings, columns per compute unit: 640x120 8,
-// 640x240 10, 832x320 9, 1024x440 24, 1152x505 19 (3 frames 1024x440: 150 us
-// against 261; 20: 564 against 587; 64: 1,900 against 1,380).
-bool chain_pays(const stixels_batch* b, int hmax, int ntasks) {
-    return hmax > 512 || (long long)ntasks <= (long long)b->num_cu * (hmax > 384 ? 18 : 9);
+// 3,766).  Below, while the launch is short: a wave per column takes as long as
+// its chain of steps however few the columns are, but costs less once every SIMD
+// has its waves.  Measured, columns per compute unit, spread / one wave: 1152x505
+// 14 561 / 638 us, 29 1,068 / 1,000, with 256 disparities 29 1,073 / 1,123, 58
+// 2,091 / 1,999; 1024x440 13 471 / 487, 16 568 / 524, 19 647 / 672, 22 741 / 689, 51
+// 1,639 / 1,270; 1024x384 6 236 / 277, 13 399 / 362; 640x240 8 177 / 192, 10 211 /
+// 206.
+bool chain_pays(const stixels_batch* b, int hmax, int dmax, int ntasks) {
+    const int per_cu = hmax > 448 && dmax > 128 ? 36 : (hmax > 384 ? 18 : 9);
+    return hmax > 512 || (long long)ntasks <= (long long)b->num_cu * per_cu;
 }
 
 int occupancy_grid(stixels_batch* b, int slots, int nch, int waves, int* grid,
@@ -268,7 +271,7 @@ int plan(stixels_batch* b, const stixels_job* jobs, int32_t n, Plan* p) {
     int rc = stage(b, jobs, n, &p->slots, &p->nch, &p->ntasks, &p->stride, &p->hmax, &dmax,
                    b->columns == 2, &p->pairs);
     if (rc != STIXELS_OK) return rc;
-    p->chain = b->waves == 0 && !p->pairs && !b->links && chain_pays(b, p->hmax, p->ntasks);
+    p->chain = b->waves == 0 && !p->pairs && !b->links && chain_pays(b, p->hmax, dmax, p->ntasks);
     if (p->chain) {
         p->waves = chain_batch_waves(p->hmax, p->ntasks, b->num_cu);
         p->stride = (long long)chain_table_floats(p->hmax, dmax);

@@ -645,10 +645,13 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
     // 1024x440, one wave per column: 1,160 -> 1,117 us, a tenth fewer vector
     // instructions.  Four chunks, 16 frames 2048x880, two waves: 5,440 -> 5,230
     // us; leaving out the column and the cost rows as well 5,500 (a branch each).
+    // Eight slots per wave keep both chunks to the end: the second copy of their
+    // steps spilled (6 frames 325x509, one wave per column, 274 -> 395 us).
+    constexpr bool TWO_ENDS = NCH == 2 && SW <= 7;
     constexpr bool TABLE4 = TALL && NCH > 2;
     int jlast[NCH];
     jlast[0] = H;
-    if constexpr (NCH == 2 || TABLE4) {
+    if constexpr (TWO_ENDS || TABLE4) {
 #pragma unroll
         for (int c = 1; c < NCH; ++c) jlast[c] = -1;
         for (int v = lane; v < H; v += 64) {
@@ -1139,6 +1142,7 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
     };
 
     using All = std::integral_constant<int, SW>;
+    using Rest = std::bool_constant<!TWO_ENDS>;   // whether the steps after jlast build two
     if constexpr (S <= 8) {
         // unrolled over the slot of row j, so that every slot test above is
         // decided at compile time (for W = 1) and the slots' gathers share
@@ -1156,7 +1160,7 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
             // steps whose base b = sj*64+jl+1 can still follow a ground stixel
             const int jgr = min(jend, max(0, vtop + 1 - sj * 64));
             int jl = 0;
-            if constexpr (NCH == 2) {
+            if constexpr (TWO_ENDS) {
                 // those that may reach the second chunk's means
                 const int jtw = min(jend, jlast[1] - sj * 64);
                 for (; jl < min(jgr, jtw); ++jl)
@@ -1164,8 +1168,8 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
                 for (; jl < jtw; ++jl)
                     step(std::false_type{}, std::true_type{}, All{}, sj, jl, sj / W, blk);
             }
-            for (; jl < jgr; ++jl) step(std::true_type{}, std::false_type{}, All{}, sj, jl, sj / W, blk);
-            for (; jl < jend; ++jl) step(std::false_type{}, std::false_type{}, All{}, sj, jl, sj / W, blk);
+            for (; jl < jgr; ++jl) step(std::true_type{}, Rest{}, All{}, sj, jl, sj / W, blk);
+            for (; jl < jend; ++jl) step(std::false_type{}, Rest{}, All{}, sj, jl, sj / W, blk);
         }
     } else if constexpr (SW <= 8) {
         // tall columns shared by several waves: one copy of the step per
@@ -1185,15 +1189,15 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
                     }
                     const int jgr = min(jend, max(0, vtop + 1 - sj * 64));
                     int jl = 0;
-                    if constexpr (NCH == 2) {
+                    if constexpr (TWO_ENDS) {
                         const int jtw = min(jend, jlast[1] - sj * 64);
                         for (; jl < min(jgr, jtw); ++jl)
                             step(std::true_type{}, std::true_type{}, lim, sj, jl, T, blk);
                         for (; jl < jtw; ++jl)
                             step(std::false_type{}, std::true_type{}, lim, sj, jl, T, blk);
                     }
-                    for (; jl < jgr; ++jl) step(std::true_type{}, std::false_type{}, lim, sj, jl, T, blk);
-                    for (; jl < jend; ++jl) step(std::false_type{}, std::false_type{}, lim, sj, jl, T, blk);
+                    for (; jl < jgr; ++jl) step(std::true_type{}, Rest{}, lim, sj, jl, T, blk);
+                    for (; jl < jend; ++jl) step(std::false_type{}, Rest{}, lim, sj, jl, T, blk);
                 }
             });
         };
