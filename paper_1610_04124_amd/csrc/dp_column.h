@@ -644,11 +644,15 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
     // chunks also its part of the object column and of the cost rows.  64 frames
     // 1024x440, one wave per column: 1,160 -> 1,117 us, a tenth fewer vector
     // instructions.  Four chunks, 16 frames 2048x880, two waves: 5,440 -> 5,230
-    // us; leaving out the column and the cost rows as well 5,500 (a branch each).
+    // us; leaving out the column and the cost rows as well 5,500 (a branch each);
+    // 4 frames 1024x440 and 256 disparities, one wave 283 -> 273, 16 frames, two
+    // waves 920 -> 886.  Up to four slots, and in tall one-wave columns, the test
+    // of every chunk costs more than it saves (640x240 287 -> 292, 2048x880 2,258
+    // -> 2,315).
     // Eight slots per wave keep both chunks to the end: the second copy of their
     // steps spilled (6 frames 325x509, one wave per column, 274 -> 395 us).
     constexpr bool TWO_ENDS = NCH == 2 && SW <= 7;
-    constexpr bool TABLE4 = TALL && NCH > 2;
+    constexpr bool TABLE4 = NCH > 2 && S > 4 && SW <= 8;
     int jlast[NCH];
     jlast[0] = H;
     if constexpr (TWO_ENDS || TABLE4) {

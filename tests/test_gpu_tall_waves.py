@@ -33,6 +33,18 @@ def frame(H, W, D, rng, invalid):
 @pytest.mark.parametrize("D", [128, 256])
 @pytest.mark.parametrize("waves", [2, 4])
 def test_tall_columns_equal_oracle(H, D, waves):
+    check(H, D, waves)
+
+
+@pytest.mark.parametrize("H", [321, 448, 512])
+@pytest.mark.parametrize("D", [200, 256])
+@pytest.mark.parametrize("waves", [1, 2, 4])
+def test_four_chunks_equal_oracle(H, D, waves):
+    """Five to eight slots, whose prior table drops chunks as the base rises."""
+    check(H, D, waves)
+
+
+def check(H, D, waves):
     import torch
     W, s = 20, 5
     rng = np.random.default_rng(H + D + waves)
