@@ -43,7 +43,7 @@ def check(m, left, right, D, p1=10, p2=120):
 @pytest.mark.parametrize("W,H,D", [
     (1, 1, 4), (23, 6, 4), (57, 9, 32), (58, 13, 32), (64, 8, 36), (131, 7, 64), (90, 5, 72),
     (149, 11, 100), (152, 4, 128), (141, 9, 128), (150, 3, 136), (275, 9, 252), (281, 10, 256),
-    (4203, 3, 32), (4100, 5, 64), (4099, 2, 128)])
+    (4203, 3, 32), (4100, 5, 64), (4099, 2, 128), (133, 70, 64)])
 @pytest.mark.parametrize("many", [False, True])
 def test_layouts_equal_oracle(W, H, D, many):
     # at most 17, 14 or 8 rows per compute unit are few
