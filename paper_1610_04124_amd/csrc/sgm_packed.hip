@@ -15,16 +15,16 @@
 // share a register (16 bits each, packed instructions): a lane holds 2 R
 // disparities, a line LPL lanes (2 R LPL >= D), a wave 64 / LPL lines.  Kept
 // relative to the last step's minimum, a step is
-//     t = C + min(L, sat(min(L(d-1), L(d+1)) + P1), P2),  L = t - min over d of t
+//     t = C + min(L, min(L(d-1), L(d+1)) + P1, P2),  L = t - min over d of t
 // (t is the path cost).  With eight disparities to a lane and 16 lanes to a line
-// that is 82 instructions for 512 disparities (95 us of a pair against 212):
+// that is 77 instructions for 512 disparities (92 us of a pair against 212):
 // 32 + 4 of them the Hamming costs, 6 the minimum over the line, which four
 // disparities to a lane pay for 256.  With few lines the chain of a row's steps
 // bounds it, and the Hamming costs go to a second wave (row_pair_pass).
 // 1024x440, 128 disparities, before (one disparity per register, four launches
-// over 16-bit sums) and now: one pair 888 / 190 us, 64 pairs 13.56 / 6.03 ms,
-// of these 3.5 the three directions (11 GB written), 2.2 the last one and the
-// selection (11 GB read, 5 TB/s), 0.4 the census.
+// over 16-bit sums) and now: one pair 888 / 185 us, 64 pairs 13.56 / 5.79 ms,
+// of these 3.3 the three directions (11 GB written), 2.2 the last one and the
+// selection (11 GB read, 5 TB/s), 0.3 the census.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -46,8 +46,13 @@ __device__ __forceinline__ uint32_t w2(u16x2 x) { return __builtin_bit_cast(uint
 __device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
     return w2(__builtin_elementwise_min(h2(a), h2(b)));
 }
-__device__ __forceinline__ uint32_t pk_add_sat(uint32_t a, uint32_t b) {
-    return w2(__builtin_elementwise_add_sat(h2(a), h2(b)));
+// Minimum of three, on whole numbers below 0x7c00: as half floats these are the
+// positive ones without infinity and NaN, in the same order (and denormals are
+// kept), so the half floats' three-way minimum does for them.
+__device__ __forceinline__ uint32_t pk_min3(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_pk_minimum3_f16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
 }
 __device__ __forceinline__ uint32_t pk_add(uint32_t a, uint32_t b) { return w2(h2(a) + h2(b)); }
 __device__ __forceinline__ uint32_t pk_sub(uint32_t a, uint32_t b) { return w2(h2(a) - h2(b)); }
@@ -66,7 +71,9 @@ __device__ __forceinline__ uint32_t dpp(uint32_t old, uint32_t x) {
 }
 
 // The lane below's and the lane above's value within a line; all ones at the
-// line's ends (edge: all ones in the line's first / last lane, else zero).
+// line's ends (edge: all ones in the line's first / last lane, else zero).  A
+// disparity has a neighbour on one side at least, so the smaller of the two is
+// always a cost.
 template <int LPL>
 __device__ __forceinline__ uint32_t from_below(uint32_t x, uint32_t edge) {
     if constexpr (LPL == 16) return dpp<0x111>(~0u, x);            // row_shr:1
@@ -155,15 +162,16 @@ struct Line {
                                          uint32_t (&t)[R]) {
         const uint32_t B = from_below<LPL>(L[R - 1], first);
         const uint32_t A = from_above<LPL>(L[0], last);
-        uint32_t m = ~0u;
+        uint32_t m;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const uint32_t dn = __builtin_amdgcn_alignbit(L[r], r > 0 ? L[r - 1] : B, 16);
             const uint32_t up = __builtin_amdgcn_alignbit(r + 1 < R ? L[r + 1] : A, L[r], 16);
-            const uint32_t n = pk_add_sat(pk_min(dn, up), P1);
-            t[r] = pk_add(pk_min(pk_min(n, L[r]), P2), C[r]);
-            m = r == 0 ? t[r] : pk_min(m, t[r]);
+            const uint32_t n = pk_add(pk_min(dn, up), P1);
+            t[r] = pk_add(pk_min3(n, L[r], P2), C[r]);
         }
+        if constexpr (R == 4) m = pk_min(pk_min3(t[0], t[1], t[2]), t[3]);
+        else m = R == 2 ? pk_min(t[0], t[R - 1]) : t[0];
         // both halves the lane's minimum: then whole words compare alike
         m = pk_min(m, __builtin_amdgcn_alignbit(m, m, 16));
         const uint32_t M = line_min<LPL>(m);
