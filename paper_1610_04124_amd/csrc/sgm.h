@@ -32,10 +32,12 @@ struct PathArgs {
 int dpl_of(int D);
 
 // Whether path costs fit a byte under this penalty; whether a call's lines are
-// few enough that all four directions go to planes (else three); and the path
-// passes with costs in bytes (sgm_packed.hip).
+// few enough that all four directions go to planes (else three); the place of
+// disparity d among a pixel's bytes; and the path passes with costs in bytes
+// (sgm_packed.hip).
 bool packed_costs(int P2);
 bool packed_four(int D, int H, int frames, int num_cu);
+int packed_place(int D, int W, int d);
 hipError_t launch_packed_paths(const uint64_t* cl, const uint64_t* cr, uint8_t* planes,
                                size_t plane, bool four, int W, int H, int frames, int D, int P1,
                                int P2, float* disp, hipStream_t st);

@@ -768,8 +768,12 @@ int stixels_sgm_debug(const stixels_sgm* m, int32_t which, void* host_dst, size_
             if (hipMemcpy(plane.data(), m->ws.planes + (size_t)(r * m->last_frames) * nd, nd,
                           hipMemcpyDeviceToHost) != hipSuccess)
                 return STIXELS_E_HIP;
-            for (size_t i = 0; i < nd; ++i)
-                dst[i] = (uint16_t)((r ? dst[i] : 0) + plane[i]);
+            const size_t D = (size_t)m->p.max_disparity;
+            for (size_t i = 0; i < nd; i += D)
+                for (size_t d = 0; d < D; ++d) {
+                    const size_t at = (size_t)stx::sgm::packed_place((int)D, m->last_W, (int)d);
+                    dst[i + d] = (uint16_t)((r ? dst[i + d] : 0) + plane[i + at]);
+                }
         }
         return STIXELS_OK;
     }

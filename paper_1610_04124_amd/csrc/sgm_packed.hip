@@ -17,12 +17,12 @@
 // relative to the last step's minimum, a step is
 //     t = C + min(L, min(L(d-1), L(d+1)) + P1, P2),  L = t - min over d of t
 // (t is the path cost).  With eight disparities to a lane and 16 lanes to a line
-// that is 77 instructions for 512 disparities (92 us of a pair against 212):
+// that is 74 instructions for 512 disparities (90 us of a pair against 212):
 // 32 + 4 of them the Hamming costs, 6 the minimum over the line, which four
 // disparities to a lane pay for 256.  With few lines the chain of a row's steps
 // bounds it, and the Hamming costs go to a second wave (row_pair_pass).
 // 1024x440, 128 disparities, before (one disparity per register, four launches
-// over 16-bit sums) and now: one pair 888 / 185 us, 64 pairs 13.56 / 5.79 ms,
+// over 16-bit sums) and now: one pair 888 / 179 us, 64 pairs 13.56 / 5.71 ms,
 // of these 3.3 the three directions (11 GB written), 2.2 the last one and the
 // selection (11 GB read, 5 TB/s), 0.3 the census.
 #include <hip/hip_runtime.h>
@@ -126,7 +126,9 @@ __device__ __forceinline__ void unrolled(F&& f) {
 // One lane's share of a line: 2 R disparities from d0.
 template <int LPL, int R>
 struct Line {
-    uint32_t L[R];                  // costs above the last minimum
+    // costs above the last minimum: disparities d0 + r and d0 + R + r share a
+    // register, so that a neighbour's are another register but at the ends
+    uint32_t L[R];
     uint32_t first, last;           // all ones in the line's first / last lane
     uint32_t past;                  // kPast where the lane lies past D
     int d0;
@@ -154,7 +156,7 @@ struct Line {
             if (!INSIDE) c[i] = x >= d0 + i ? c[i] : kCostOut + past;
         }
 #pragma unroll
-        for (int r = 0; r < R; ++r) C[r] = c[2 * r] | (c[2 * r + 1] << 16);
+        for (int r = 0; r < R; ++r) C[r] = c[r] | (c[R + r] << 16);
     }
 
     // one step: t becomes the path costs
@@ -165,8 +167,8 @@ struct Line {
         uint32_t m;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const uint32_t dn = __builtin_amdgcn_alignbit(L[r], r > 0 ? L[r - 1] : B, 16);
-            const uint32_t up = __builtin_amdgcn_alignbit(r + 1 < R ? L[r + 1] : A, L[r], 16);
+            const uint32_t dn = r > 0 ? L[r - 1] : __builtin_amdgcn_alignbit(L[R - 1], B, 16);
+            const uint32_t up = r + 1 < R ? L[r + 1] : __builtin_amdgcn_alignbit(A, L[0], 16);
             const uint32_t n = pk_add(pk_min(dn, up), P1);
             t[r] = pk_add(pk_min3(n, L[r], P2), C[r]);
         }
@@ -184,18 +186,16 @@ struct Line {
 // columns of 256 disparities, four lines); kNowhere is past it.
 constexpr uint32_t kRange = 1u << 24, kNowhere = 1u << 31;
 
-// The lane's 2 R bytes of path costs.
+// The lane's 2 R bytes of path costs, in the order of packed_place().
 template <int R>
 struct Bytes {
     static constexpr int kWords = R > 1 ? R / 2 : 1;
     uint32_t b[kWords];
     __device__ __forceinline__ void pack(const uint32_t (&t)[R]) {
-        if constexpr (R == 1)
-            b[0] = __builtin_amdgcn_perm(0u, t[0], 0x0c0c0200u);
+        if constexpr (R == 1) b[0] = __builtin_amdgcn_perm(0u, t[0], 0x0c0c0200u);
         else
 #pragma unroll
-            for (int i = 0; i < kWords; ++i)
-                b[i] = __builtin_amdgcn_perm(t[2 * i + 1], t[2 * i], 0x06040200u);
+            for (int i = 0; i < kWords; ++i) b[i] = t[2 * i] | (t[2 * i + 1] << 8);
     }
     // to base + off, or nowhere past kRange: a buffer's range check instead of
     // a branch, so that steps stay one block that the compiler can interleave
@@ -220,10 +220,11 @@ struct Bytes {
             b[1] = v[1];
         }
     }
-    // disparities 2 r and 2 r + 1, 16 bits each
+    // disparities d0 + r and d0 + R + r, 16 bits each
     __device__ __forceinline__ uint32_t half(int r) const {
-        return (r & 1) ? __builtin_amdgcn_perm(0u, b[r / 2], 0x0c030c02u)
-                       : __builtin_amdgcn_perm(0u, b[r / 2], 0x0c010c00u);
+        if constexpr (R == 1) return __builtin_amdgcn_perm(0u, b[0], 0x0c010c00u);
+        return (r & 1) ? __builtin_amdgcn_perm(0u, b[r / 2], 0x0c030c01u)
+                       : __builtin_amdgcn_perm(0u, b[r / 2], 0x0c020c00u);
     }
 };
 
@@ -625,8 +626,8 @@ struct Selection {
         uint32_t key[2 * R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            key[2 * r] = (s[r] << 16) | (uint32_t)(ln.d0 + 2 * r) | none;
-            key[2 * r + 1] = (s[r] & 0xffff0000u) | (uint32_t)(ln.d0 + 2 * r + 1) | none;
+            key[r] = (s[r] << 16) | (uint32_t)(ln.d0 + r) | none;
+            key[R + r] = (s[r] & 0xffff0000u) | (uint32_t)(ln.d0 + R + r) | none;
         }
         uint32_t k = key[0];
 #pragma unroll
@@ -849,6 +850,16 @@ hipError_t launch_few(const PackedArgs& a, hipStream_t st) {
 
 bool packed_costs(int P2) { return kCostOut + P2 <= 255; }
 
+// Eight disparities to a lane: lanes then end at D, and four rows of up to 4096
+// columns to a wave have their selection state in LDS.
+static bool packed_eights(int D, int W) { return D % 8 == 0 && D > 64 && (D > 128 || W <= 4096); }
+
+int packed_place(int D, int W, int d) {
+    // a lane's eight: 0 1 4 5, 2 3 6 7
+    constexpr int place[8] = {0, 1, 4, 5, 2, 3, 6, 7};
+    return packed_eights(D, W) ? (d & ~7) | place[d & 7] : d;
+}
+
 // Few lines are all four directions side by side: while a compute unit has at
 // most 17 rows of 64 disparities, 14 of 128 or 8 of 256.  On 256 of them, us with
 // few / many lines' kernels: 640x240 and 32 disparities 289 / 347 at 16 pairs,
@@ -864,7 +875,7 @@ hipError_t launch_packed_paths(const uint64_t* cl, const uint64_t* cr, uint8_t* 
                                size_t plane, bool four, int W, int H, int frames, int D, int P1,
                                int P2, float* disp, hipStream_t st) {
     const PackedArgs a{cl, cr, planes, plane, disp, W, H, D, P1, P2, frames};
-    const bool eights = D % 8 == 0;                   // lanes of eight disparities end at D
+    const bool eights = packed_eights(D, W);
     if (four) {
         if (D <= 32) return launch_few<16, 1>(a, st);
         if (D <= 64) return launch_few<16, 2>(a, st);
@@ -875,9 +886,7 @@ hipError_t launch_packed_paths(const uint64_t* cl, const uint64_t* cr, uint8_t* 
     // 4096 columns
     if (D <= 32 && W <= 4096) return launch_many<16, 1, 8>(a, st);
     if (D <= 64 && W <= 4096) return launch_many<16, 2, 8>(a, st);
-    if (D <= 128)
-        return eights && D > 64 && W <= 4096 ? launch_many<16, 4, 8>(a, st)
-                                             : launch_many<32, 2, 8>(a, st);
+    if (D <= 128) return eights ? launch_many<16, 4, 8>(a, st) : launch_many<32, 2, 8>(a, st);
     return eights ? launch_many<32, 4, 8>(a, st) : launch_many<64, 2, 8>(a, st);
 }
 
