@@ -214,6 +214,15 @@ __attribute__((amdgpu_waves_per_eu(4))) void chain_frame_kernel(const ChainArgs)
     const int tid = threadIdx.x, lane = tid & 63, nt = (int)blockDim.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = nt >> 6;
     unsigned int own = 0, own4 = 0;              // kArena: this workgroup's table space
+#ifdef STX_PHASE_TIMING
+    // wave 0 stamps the shader clock at each phase boundary of a batch's column
+    const unsigned long long t_entry = __builtin_amdgcn_s_memtime();
+    unsigned long long* phases = nullptr;
+    unsigned long long t0 = 0, t1 = 0, t2 = 0, t3 = 0, t4 = 0;
+    auto phase_add = [&](int slot, unsigned long long v) {
+        if (MODE == kBatch && tid == 0 && phases) atomicAdd(phases + slot, v);
+    };
+#endif
     for (bool once = true; MODE != kFrame || once; once = false) {
         int job = 0, col = (int)blockIdx.x;
         if constexpr (MODE != kFrame) {
@@ -241,6 +250,10 @@ __attribute__((amdgpu_waves_per_eu(4))) void chain_frame_kernel(const ChainArgs)
         }
         const Const<JobDesc> job_at = MODE == kBatch ? in_const(again(a)->jobs) + job : &a->job;
         const int H = job_at->H, D = job_at->D, stride = H + 1;
+#ifdef STX_PHASE_TIMING
+        phases = job_at->phase;
+        t0 = __builtin_amdgcn_s_memtime();
+#endif
         ChainLds L = chain_lds(mem, H);
         {   // the overlay may need more room than the ring and the records
             const int more = overlay_bytes(H, D, nw) - ring_rec_bytes(H);
@@ -283,6 +296,9 @@ __attribute__((amdgpu_waves_per_eu(4))) void chain_frame_kernel(const ChainArgs)
             if (anyinv) atomicOr(&red[2], 1);
         }
         __syncthreads();
+#ifdef STX_PHASE_TIMING
+        t1 = __builtin_amdgcn_s_memtime();
+#endif
         // object means lie in [smallest, largest valid q]; a stixel without
         // valid pixels has mean 0
         int fmin = __builtin_amdgcn_readfirstlane(red[2] ? 0 : red[0]);
@@ -344,6 +360,9 @@ __attribute__((amdgpu_waves_per_eu(4))) void chain_frame_kernel(const ChainArgs)
                 a->ex.range[2 * col + 1] = fmax;
             }
         }
+#ifdef STX_PHASE_TIMING
+        t2 = __builtin_amdgcn_s_memtime();
+#endif
         float* const stg = stage + wave * (kMaxDisparity + 4);
         if (H <= 256) object_rows<1>(again(job_at), qs, stg, edges, &red[3], po, fmin, fmax);
         else if (H <= 512) object_rows<2>(again(job_at), qs, stg, edges, &red[3], po, fmin, fmax);
@@ -359,7 +378,13 @@ __attribute__((amdgpu_waves_per_eu(4))) void chain_frame_kernel(const ChainArgs)
             chain_bounds(c, L, wave, nw);
             __syncthreads();
         }
+#ifdef STX_PHASE_TIMING
+        t3 = __builtin_amdgcn_s_memtime();
+#endif
         chain_solve(c, L, prior, [&]() {
+#ifdef STX_PHASE_TIMING
+            t4 = __builtin_amdgcn_s_memtime();
+#endif
             const Const<JobDesc> J = again(job_at);
             ColumnOut out;
             out.count = J->counts + col;
@@ -369,8 +394,22 @@ __attribute__((amdgpu_waves_per_eu(4))) void chain_frame_kernel(const ChainArgs)
             out.cap = J->cap;
             return out;
         });
+#ifdef STX_PHASE_TIMING
+        if (tid == 0) {
+            __builtin_amdgcn_s_waitcnt(0);
+            phase_add(kPhaseReduce, t1 - t0);
+            phase_add(kPhaseScans, t2 - t1);
+            phase_add(kPhaseObjectTable, t3 - t2);
+            phase_add(kPhaseRecurrence, t4 - t3);
+            phase_add(kPhaseBacktrack, __builtin_amdgcn_s_memtime() - t4);
+            phase_add(kPhaseTasks, 1ull);
+        }
+#endif
         if constexpr (MODE != kFrame) __syncthreads();   // the next column reuses it all
     }
+#ifdef STX_PHASE_TIMING
+    phase_add(kPhaseLifetime, __builtin_amdgcn_s_memtime() - t_entry);
+#endif
 }
 
 namespace {
