@@ -646,13 +646,13 @@ __device__ __forceinline__ void solve_column(const int H, const int vtop, const 
     // instructions.  Four chunks, 16 frames 2048x880, two waves: 5,440 -> 5,230
     // us; leaving out the column and the cost rows as well 5,500 (a branch each);
     // 4 frames 1024x440 and 256 disparities, one wave 283 -> 273, 16 frames, two
-    // waves 920 -> 886.  Up to four slots, and in tall one-wave columns, the test
-    // of every chunk costs more than it saves (640x240 287 -> 292, 2048x880 2,258
-    // -> 2,315).
+    // waves 920 -> 886.  Up to six slots, and in tall one-wave columns, the test
+    // of every chunk costs more than it saves (640x240 287 -> 292, 1342x307 388 ->
+    // 395, 2048x880 2,258 -> 2,315).
     // Eight slots per wave keep both chunks to the end: the second copy of their
     // steps spilled (6 frames 325x509, one wave per column, 274 -> 395 us).
     constexpr bool TWO_ENDS = NCH == 2 && SW <= 7;
-    constexpr bool TABLE4 = NCH > 2 && S > 4 && SW <= 8;
+    constexpr bool TABLE4 = NCH > 2 && S > 6 && SW <= 8;
     int jlast[NCH];
     jlast[0] = H;
     if constexpr (TWO_ENDS || TABLE4) {
