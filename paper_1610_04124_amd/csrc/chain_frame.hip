@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <climits>
 
+#include "arena.h"
 #include "chain.h"
 #include "chain_frame.h"
 
@@ -208,7 +209,6 @@ __attribute__((amdgpu_waves_per_eu(4))) void chain_frame_kernel(const ChainArgs)
     __shared__ int red[4];                       // smallest, largest, any invalid; next object row
     __shared__ int task;
     __shared__ unsigned int place;               // kArena: in 16-byte units
-    constexpr unsigned int kNoPlace = ~0u;
     // the arguments where they lie
     const Const<ChainArgs> a = (Const<ChainArgs>)__builtin_amdgcn_kernarg_segment_ptr();
     const int tid = threadIdx.x, lane = tid & 63, nt = (int)blockDim.x;
@@ -315,10 +315,15 @@ __attribute__((amdgpu_waves_per_eu(4))) void chain_frame_kernel(const ChainArgs)
             if (own4 < need4) {
                 if (tid == 0) {
                     const Const<ChainArgs> A = again(a);
-                    const unsigned int at = atomicAdd(&A->head->used4, need4);
-                    const bool ok = at + need4 <= A->room4 && at + need4 >= at;
-                    place = ok ? at : kNoPlace;
-                    if (!ok) A->rest[atomicAdd(&A->head->nrest, 1u)] = col;
+                    unsigned int* const used4 = &A->head->used4;
+                    place = arena_take(
+                        A->room4, need4,
+                        [&]() {
+                            return __hip_atomic_load(used4, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+                        },
+                        [&](unsigned int n) { return atomicAdd(used4, n); });
+                    if (place == kNoPlace) A->rest[atomicAdd(&A->head->nrest, 1u)] = col;
                 }
                 __syncthreads();
                 const unsigned int at = (unsigned int)__builtin_amdgcn_readfirstlane((int)place);
