@@ -1,0 +1,115 @@
+"""The kernels that a default frame does not launch, against the CPU oracle bit
+for bit.  With neither waves nor placement set, stixels_compute takes a column
+through every stage in one launch; the separate kernels (reduction, tables,
+one-wave recurrence) run when waves are set, the table kernel and the spread
+recurrence over its tables with online object costs, and the persistent kernel
+over one frame's columns on the fused path with waves set."""
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+import paper_1610_04124_amd as P
+from paper_1610_04124_amd import binding as B
+from gpu_helpers import announce, assert_frames_equal, gpu_frame
+from test_gpu_chain import frame_and_params
+from test_gpu_parity import STAGE_CASES, handle_for, small_cases
+from test_gpu_paths import fused_cases, fused_frame
+
+pytestmark = pytest.mark.gpu
+
+#: how the separate kernels are reached: waves set, or online object costs
+WAYS = ["one wave", "online costs"]
+
+
+def choose(h, way):
+    if way == "one wave":
+        h.set_waves(1)
+    else:
+        h.set_object_lut(1)
+
+
+#: heights around the table kernel's 256-row groups, its four rows a lane, and
+#: the 32-row entries of the recurrence's bounds
+TABLE_CASES = STAGE_CASES + [
+    (30, 31, 3, 16, 0, 9), (30, 32, 3, 16, 1, 10), (45, 253, 5, 64, 0, 11), (45, 255, 5, 256, 0, 12),
+    (45, 256, 5, 128, 1, 13), (45, 257, 5, 128, 0, 14), (45, 510, 5, 256, 0, 15),
+    (45, 512, 5, 64, 0, 16), (45, 513, 5, 64, 0, 17), (25, 769, 5, 256, 0, 18),
+    (25, 1022, 5, 128, 0, 19), (25, 1024, 5, 256, 0, 20),
+]
+
+
+@pytest.mark.parametrize("way", WAYS)
+@pytest.mark.parametrize("W,H,s,D,mode,seed", TABLE_CASES)
+def test_tables_of_the_separate_kernels(W, H, s, D, mode, seed, way):
+    """Reduced pixels, small prefix tables, ranges, object prefix rows, and the
+    frame that the recurrence makes of them."""
+    announce(f"tables, {way}: W={W} H={H} s={s} D={D} mode={mode} seed={seed}")
+    p, h = handle_for(W, H, s=s, D=D, reduce_mode=mode,
+                      camera=dict(synth.CAMERA_1024x440, horizon_row=float(H // 3)))
+    disp = synth.random_columns_frame(seed, W, H, D)
+    choose(h, way)
+    assert_frames_equal(gpu_frame(h, disp), oracle.frame(p, disp), f"{way} {W}x{H}")
+    q = oracle.reduce(p, disp)
+    assert np.array_equal(h.debug_stage(B.STAGE_REDUCED, W, H).astype(np.int32), q)
+    pre = h.debug_stage(B.STAGE_PREFIX, W, H).astype(np.float64)
+    rng = h.debug_stage(B.STAGE_RANGE, W, H)
+    po = h.debug_stage(B.STAGE_OBJECT_PREFIX, W, H).astype(np.float64)
+    for i in range(W // s):
+        c = oracle.column(p, q[i])
+        for t, want in enumerate((c["PG"], c["PS"], 2 * c["PD"] + c["PN"], 2 * c["PN"])):
+            assert np.array_equal(pre[t, i], want), (i, t)
+        valid = q[i][q[i] >= 0]
+        lo, hi = (int(valid.min()), int(valid.max())) if valid.size else (0, 0)
+        lo = lo if valid.size == H else 0
+        assert tuple(rng[i]) == (lo, hi)
+        assert np.array_equal(po[i, : hi - lo + 1], c["PO"][lo:hi + 1]), i
+
+
+@pytest.mark.parametrize("way", WAYS)
+@pytest.mark.parametrize("W,H,s,D,mode,seed", small_cases())
+def test_adversarial_frames(W, H, s, D, mode, seed, way):
+    announce(f"adversarial, {way}: W={W} H={H} s={s} D={D} mode={mode} seed={seed}")
+    cam = dict(synth.CAMERA_1024x440, horizon_row=float(int(seed % max(H, 1))))
+    p, h = handle_for(W, H, s=s, D=D, reduce_mode=mode, camera=cam)
+    disp = synth.random_columns_frame(seed, W, H, D)
+    choose(h, way)
+    assert_frames_equal(gpu_frame(h, disp), oracle.frame(p, disp), f"{way} {W}x{H}")
+
+
+@pytest.mark.parametrize("W,H,s,D,mode,seed", fused_cases())
+def test_fused_frame_of_one_wave(W, H, s, D, mode, seed):
+    """The persistent kernel over one frame's columns."""
+    announce(f"fused, one wave: W={W} H={H} s={s} D={D} mode={mode} seed={seed}")
+    cam = dict(synth.CAMERA_1024x440, horizon_row=float(seed % max(H, 1)))
+    p, h = handle_for(W, H, s=s, D=D, reduce_mode=mode, camera=cam)
+    disp = synth.random_columns_frame(seed, W, H, D)
+    assert_frames_equal(fused_frame(h, disp, waves=1), oracle.frame(p, disp), f"fused {W}x{H}")
+
+
+@pytest.mark.parametrize("H,D,kind", [
+    (1, 16, "columns"), (8, 16, "noise"), (17, 64, "columns"), (63, 64, "one object"),
+    (64, 64, "columns"), (65, 64, "object steps"), (128, 128, "one object"), (129, 128, "columns"),
+    (193, 200, "columns"), (257, 128, "one object"), (449, 128, "object steps"),
+    (513, 256, "one object"), (705, 128, "object steps"), (880, 256, "ramp"),
+    (897, 256, "one object"), (961, 256, "columns"), (1024, 256, "object steps"),
+])
+def test_spread_recurrence_over_tables(H, D, kind):
+    """The recurrence spread over a workgroup, from tables in memory."""
+    announce(f"spread over tables H={H} D={D} {kind}")
+    p, disp = frame_and_params(H, D, kind)
+    h = P.Stixels(p)
+    choose(h, "online costs")
+    assert_frames_equal(gpu_frame(h, disp), oracle.frame(p, disp), f"{kind} {H}")
+    h.close()
+
+
+@pytest.mark.parametrize("cols", [256, 257])
+def test_spread_recurrence_over_tables_workgroup_sizes(cols):
+    announce(f"spread over tables, columns {cols}")
+    p, disp = frame_and_params(200, 64, "object steps", s=2, cols=cols)
+    h = P.Stixels(p)
+    choose(h, "online costs")
+    assert_frames_equal(gpu_frame(h, disp), oracle.frame(p, disp), f"{cols} columns")
+    h.close()
