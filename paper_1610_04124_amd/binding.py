@@ -302,6 +302,8 @@ class Stixels:
         # disparity bins: max_disparity px in bins of 2^-subpixel_log2 px
         self.D = bins(params)
         self.max_height = int(params["max_height"])
+        # costs on the 2^-g grid (a negative cost_grid_log2 keeps them off any)
+        self.on_grid = int(params["cost_grid_log2"]) >= 0
 
     def close(self):
         if getattr(self, "h", None):

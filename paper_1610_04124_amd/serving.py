@@ -142,7 +142,13 @@ class GpuExecutor:
         most SHORT per compute unit: a launch that short spreads each column
         over a workgroup whatever its height, and two such launches in a row
         leave the chip partly idle twice (two frames 1024x440 and one 1280x720:
-        80 and 103 us one after the other)."""
+        80 and 103 us one after the other).  That holds for costs on the grid:
+        one frame with costs off it sends its whole launch to the one-wave
+        kernel with stored links, sized for the tallest frame, so classes join
+        only if every frame of both is on the grid."""
+        def on_grid(rs):
+            return all(getattr(self.cameras[r.camera].handle, "on_grid", True) for r in rs)
+
         groups = {}
         for r in reqs:
             groups.setdefault(self.cameras[r.camera].height_class(), []).append(r)
@@ -153,7 +159,7 @@ class GpuExecutor:
                 hmax, dmax, cols = self.classes[top]
                 both = members + groups[k]
                 ncols = sum(self.cameras[r.camera].ncols() for r in both)
-                if (self.layout_for(top) == self.layout_for(k) == (1, 0, 0)
+                if (self.layout_for(top) == self.layout_for(k) == (1, 0, 0) and on_grid(both)
                         and len(both) <= self.max_frames
                         and ncols <= min(self.SHORT * self.num_cu, self.max_frames * cols)
                         and max(self.cameras[r.camera].handle.D for r in groups[k]) <= dmax):

@@ -59,6 +59,28 @@ def test_limits_of_the_taller_class():
     assert groups(executor(CAMERAS, layout={MID: (1, 2, 0)}), [0, 1]) == [(TALL, [1]), (MID, [0])]
 
 
+def test_costs_off_the_grid_keep_classes_apart():
+    # one frame off the grid would take the whole launch off the spread kernel
+    for off in ([0], [1], [0, 1]):
+        ex = executor(CAMERAS)
+        for c in off:
+            ex.cameras[c].handle.on_grid = False
+        assert groups(ex, [0, 1]) == [(TALL, [1]), (MID, [0])]
+        # the classes below it may still join each other
+        want = [(TALL, [1]), (MID, [0]), (LOW, [2])] if 0 in off else [(TALL, [1]), (MID, [0, 2])]
+        assert groups(ex, [0, 1, 2]) == want
+
+
+@pytest.mark.gpu
+def test_handles_say_whether_costs_are_on_the_grid():
+    import synth
+    import paper_1610_04124_amd as P
+    for g in (-1, 0, 10):
+        h = P.Stixels(synth.make_params(max_width=64, max_height=32, flags=1, cost_grid_log2=g))
+        assert h.on_grid == (g >= 0)
+        h.close()
+
+
 @pytest.mark.gpu
 def test_mixed_heights_in_one_launch_equal_oracle():
     import torch
