@@ -275,7 +275,7 @@ int plan(stixels_batch* b, const stixels_job* jobs, int32_t n, Plan* p) {
     if (p->chain) {
         p->waves = chain_batch_waves(p->hmax, p->ntasks, b->num_cu);
         p->stride = (long long)chain_table_floats(p->hmax, dmax);
-        long long g = std::min<long long>((long long)chain_batch_per_cu(p->waves) * b->num_cu,
+        long long g = std::min<long long>((long long)chain_batch_per_cu(p->hmax, p->waves) * b->num_cu,
                                           (long long)(b->scratch_floats / (size_t)p->stride));
         if (b->cfg.workgroups > 0) g = std::min<long long>(g, b->cfg.workgroups);
         p->grid = (int)std::min<long long>(g, p->ntasks);

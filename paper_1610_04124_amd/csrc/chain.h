@@ -70,6 +70,14 @@ __host__ __device__ constexpr int chain_waves(int H, int most) {
     return n;
 }
 
+// Workgroups of `waves` waves and `lds` bytes (their static part included) that
+// a compute unit of gfx950 holds: 16 waves, the kernels taking up to 128
+// registers a lane, and 160 KB of LDS in blocks of 1,280 bytes.
+__host__ __device__ constexpr int chain_resident(int waves, int lds) {
+    const int by_lds = 160 * 1024 / ((lds + 1279) / 1280 * 1280), by_waves = 16 / waves;
+    return by_lds < by_waves ? by_lds : by_waves;
+}
+
 struct ChainFlags {
     int prep[kRing];               // group held by a ring place, plus one
     int done;                      // groups the chain has finished

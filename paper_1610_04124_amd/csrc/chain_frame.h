@@ -40,7 +40,7 @@ hipError_t launch_chain_batch(const JobDesc* jobs, const int2* tasks, int ntasks
 // Waves of a workgroup for a launch of ntasks columns, and how many such
 // workgroups stay resident on a compute unit.
 int chain_batch_waves(int hmax, int ntasks, int num_cu);
-int chain_batch_per_cu(int waves);
+int chain_batch_per_cu(int hmax, int waves);
 
 // Lets the current device's launches of these kernels use up to lds_per_block
 // bytes of LDS (once per device; repeating it is harmless).

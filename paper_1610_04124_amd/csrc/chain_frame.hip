@@ -85,6 +85,10 @@ __host__ __device__ constexpr int lds_bytes(int H, int D, int nw) {
     return (int)chain_lds_bytes(H) + (more > 0 ? ((more + 15) & ~15) : 0);
 }
 
+// ... and the kernels' own variables: four words, and two more, padded, where
+// columns are handed out.
+constexpr int static_lds(bool frame) { return frame ? 16 : 32; }
+
 // Small prefix table t of a column from its pixels (one wave): entries into a
 // component of an LDS float4 array, and to memory when out is given.
 __device__ __forceinline__ void small_table(Const<JobDesc> J, const int16_t* qs, const int t,
@@ -430,11 +434,21 @@ hipError_t start(const ChainArgs& a, int grid, int waves, int lds, hipStream_t s
 
 // A workgroup has 16 waves where there is a compute unit for each, else 8, two
 // to a compute unit (2048x880, 409 columns: 242 us with 16 waves, 201 with 8, at
-// the same stage of the kernel).  Four halves of a group's gathers in flight
-// instead of two groups' would let three such workgroups in (80 registers a
-// lane): 16 frames 1024x440 took 508 us instead of 476, one frame 96 instead
-// of 78.
-int frame_waves_of(int ncols, int H, int num_cu) { return chain_waves(H, ncols <= num_cu ? 16 : 8); }
+// the same stage of the kernel), as long as their LDS lets two in: a frame's
+// columns up to 889 rows, others up to 888.  Above, one is there whatever its
+// waves, and has 16: 8 / 16 waves on frames of 2048 columns' width and 256
+// disparities took, with 3-pixel columns, 388 / 346 us at 896 rows and 468 / 413
+// at 1024 (889 rows: two of 8 waves 314, one of 16 340), 16 frames at once 5,466 /
+// 4,817 at 889 and 6,546 / 5,523 at 1024.  Four halves of a group's gathers in
+// flight instead of two groups' would let three workgroups of 8 in (80 registers
+// a lane): 16 frames 1024x440 took 508 us instead of 476, one frame 96 instead of
+// 78.
+int frame_waves_of(int ncols, int H, int D, int num_cu, bool frame) {
+    const int few = chain_waves(H, 8);
+    const bool alone = ncols <= num_cu ||
+                       chain_resident(few, lds_bytes(H, D, few) + static_lds(frame)) < 2;
+    return alone ? chain_waves(H, 16) : few;
+}
 
 constexpr size_t kHeadBytes = 256;
 size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -448,7 +462,7 @@ hipError_t launch_chain_frame(const JobDesc& job, float* po, const ChainExports&
     a.ex = ex;
     a.po = po;
     a.stride = (long long)chain_table_floats(job.H, job.D);
-    const int nw = frame_waves_of(job.ncols, job.H, num_cu);
+    const int nw = frame_waves_of(job.ncols, job.H, job.D, num_cu, true);
     return start<kFrame>(a, job.ncols, nw, lds_bytes(job.H, job.D, nw), st);
 }
 
@@ -478,9 +492,9 @@ hipError_t launch_chain_arena(const JobDesc& job, void* ws, size_t ws_bytes, int
     a.room4 = (unsigned int)((ws_bytes - base) / 16);
     hipLaunchKernelGGL(arena_reset_kernel, dim3(1), dim3(1), 0, st, a.head);
     hipError_t e = hipGetLastError();
-    const int nw = frame_waves_of(job.ncols, job.H, num_cu);
+    const int nw = frame_waves_of(job.ncols, job.H, job.D, num_cu, false);
     const int lds = lds_bytes(job.H, job.D, nw);
-    const int per_cu = nw > 8 ? 1 : 2;
+    const int per_cu = chain_resident(nw, lds + static_lds(false));
     if (e == hipSuccess) e = start<kArena>(a, std::min(job.ncols, per_cu * num_cu), nw, lds, st);
     if (e == hipSuccess)
         e = start<kArenaRest>(a, (int)std::min<size_t>(tables, (size_t)std::min(job.ncols, num_cu)),
@@ -489,9 +503,11 @@ hipError_t launch_chain_arena(const JobDesc& job, void* ws, size_t ws_bytes, int
 }
 
 int chain_batch_waves(int hmax, int ntasks, int num_cu) {
-    return frame_waves_of(ntasks, hmax, num_cu);
+    return frame_waves_of(ntasks, hmax, kMaxDisparity, num_cu, false);
 }
-int chain_batch_per_cu(int waves) { return waves > 8 ? 1 : 2; }
+int chain_batch_per_cu(int hmax, int waves) {
+    return chain_resident(waves, lds_bytes(hmax, kMaxDisparity, waves) + static_lds(false));
+}
 
 hipError_t launch_chain_batch(const JobDesc* jobs, const int2* tasks, int ntasks,
                               unsigned int* counter, float* scratch, long long stride, int hmax,

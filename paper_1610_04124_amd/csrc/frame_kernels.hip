@@ -428,9 +428,13 @@ hipError_t launch_dp(const DeviceModel& m, const FrameWorkspace& ws, int H, int 
     a.lds_floats = 0;
     a.prior = m.prior;
     if (waves == 0) {
+        // as in chain_frame.hip: 16 waves where a column has a compute unit to
+        // itself, by the columns' number or because no second one's LDS fits
+        const int lds = (int)chain_lds_bytes(H);
+        const bool alone = ncols <= num_cu || chain_resident(8, lds) < 2;
         void* args[] = {&a};
         return hipLaunchKernel(reinterpret_cast<const void*>(&chain_kernel), dim3(ncols),
-                               dim3(64 * chain_waves(H, ncols <= num_cu ? 16 : 8)), args, chain_lds_bytes(H), st);
+                               dim3(64 * chain_waves(H, alone ? 16 : 8)), args, (size_t)lds, st);
     }
     const int slots = kernel_slots(H), nch = kernel_chunks(m.D);
     // the LDS copy exists for one wave per column and d_range <= 128 only:
