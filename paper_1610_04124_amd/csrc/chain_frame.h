@@ -28,6 +28,8 @@ hipError_t launch_chain_frame(const JobDesc& job, float* po, const ChainExports&
 // One frame with its tables in a workspace of ws_bytes that may hold fewer
 // than its columns (bytes needed: chain_arena_bytes).
 size_t chain_arena_bytes(int ncols, int H, int D, int tables);
+// Whether that pays against a wave per column in the same workspace.
+bool chain_arena_pays(int ncols, int H, int D, size_t ws_bytes, int num_cu);
 hipError_t launch_chain_arena(const JobDesc& job, void* ws, size_t ws_bytes, int num_cu,
                               hipStream_t st);
 

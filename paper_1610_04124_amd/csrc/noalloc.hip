@@ -88,7 +88,8 @@ extern "C" int stixels_compute_noalloc(stixels_handle* h, const float* d_dispari
     persist::JobDesc job = persist::make_job_desc(h, d_disparity, width, height, *out);
     const int waves = frame_waves(h->waves, height, ncols, h->num_cu);
     int grid = 0;
-    if (h->prior.exact && h->waves == 0)
+    if (h->prior.exact && h->waves == 0 &&
+        persist::chain_arena_pays(ncols, height, h->D, kNoAllocScratchBytes, h->num_cu))
         e = persist::launch_chain_arena(job, ws, kNoAllocScratchBytes, h->num_cu, st);
     else
         e = persist::launch_frame_fused(job, ws, kNoAllocScratchBytes, waves, h->num_cu, st, &grid);

@@ -66,3 +66,35 @@ def test_more_columns_than_a_count_of_requests_holds():
         setattr(first, k, t[0].cpu())
     assert_frames_equal(first.to_host(), ref, "the first columns")
     h.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("W,H,D", [
+    (2000, 64, 128), (2000, 96, 128), (2000, 97, 128), (4300, 64, 256), (4300, 65, 256),
+    (4000, 64, 256), (5000, 16, 256), (1000, 32, 256),
+])
+def test_frames_on_both_sides_of_the_line(W, H, D):
+    """Columns spread over workgroups or a wave each, by rows, bins and columns."""
+    import torch
+    import oracle
+    import synth
+    import paper_1610_04124_amd as P
+    from gpu_helpers import announce, assert_frames_equal, device, to_device
+
+    tile = 50
+    p = synth.make_params(camera=dict(synth.CAMERA_1024x440, horizon_row=float(H // 3)),
+                          stixel_width=1, max_disparity=D, max_width=W, max_height=H, flags=1)
+    disp = synth.random_columns_frame(W + H, tile, H, D)
+    ref = oracle.frame(p, disp)
+    h = P.Stixels(p)
+    frame = to_device(disp).repeat(1, W // tile)
+    announce(f"noalloc {W}x{H} D={D} s=1")
+    for _ in range(2):                        # the workspace holds the last call's tables
+        out = P.FrameOutput(W, H, device())
+        out.counts.fill_(-7)
+        h.compute_noalloc(frame, out)
+        torch.cuda.synchronize()
+        host = out.to_host()
+        for i in range(0, W, tile):
+            assert_frames_equal({k: v[i:i + tile] for k, v in host.items()}, ref, f"from {i}")
+    h.close()
