@@ -113,14 +113,26 @@ int batch_waves_for(const stixels_batch* b, int slots) {
 // with two waves a column; 32 frames 1280x720, 8,192 columns: 1,952 against
 // 3,766).  Below, while the launch is short: a wave per column takes as long as
 // its chain of steps however few the columns are, but costs less once every SIMD
-// has its waves.  Measured, columns per compute unit, spread / one wave: 1152x505
-// 14 561 / 638 us, 29 1,068 / 1,000, with 256 disparities 29 1,073 / 1,123, 58
-// 2,091 / 1,999; 1024x440 13 471 / 487, 16 568 / 524, 19 647 / 672, 22 741 / 689, 51
-// 1,639 / 1,270; 1024x384 6 236 / 277, 13 399 / 362; 640x240 8 177 / 192, 10 211 /
-// 206.
+// has its waves.  The line is where that form first takes less, by the rows' 64-row
+// slots and the prior table's chunks.  Measured, one wave's time over the spread
+// form's at so many columns per compute unit:
+//   65-320 rows     6 1.03-1.15  7 0.92-1.02   8 0.90-0.98; over 128 bins 6 1.04-1.25  7 0.96-1.04
+//                   8 0.93-1.00
+//   321-384         7 1.01-1.02  8 0.97-0.98  10 0.93-0.96; over 128 bins 9 1.03-1.05 10 0.98-1.00
+//   385-448        10 0.98-1.02 11 0.93-0.99  16 0.89-0.98  18 0.94-1.05; over 128 bins 10 1.06-1.13
+//                  16 0.96-1.06 18 1.02-1.12  22 0.95-1.05
+//   449-512        11 0.97-1.05 18 1.01-1.06  20 0.91-0.97; over 128 bins 24 0.97-1.03 28 0.99-1.05
+//                  32 0.96-1.01 36 0.93-0.99
+// (The dips inside a line's range are whole rounds of either form.)  Up to 64
+// rows four workgroups share a compute unit: 1.07-1.30 up to 10 columns.
 bool chain_pays(const stixels_batch* b, int hmax, int dmax, int ntasks) {
-    const int per_cu = hmax > 448 && dmax > 128 ? 36 : (hmax > 384 ? 18 : 9);
-    return hmax > 512 || (long long)ntasks <= (long long)b->num_cu * per_cu;
+    if (hmax > 512) return true;
+    const int slots = (hmax + 63) / 64;
+    //                          rows up to  64  128  192  256  320  384  448  512
+    static constexpr int kNarrow[8] = {  9,   6,   6,   6,   6,   7,  10,  18};
+    static constexpr int kWide[8]   = {  9,   7,   7,   7,   7,   9,  18,  28};
+    const int per_cu = (dmax > 128 ? kWide : kNarrow)[slots - 1];
+    return (long long)ntasks <= (long long)b->num_cu * per_cu;
 }
 
 int occupancy_grid(stixels_batch* b, int slots, int nch, int waves, int* grid,

@@ -95,9 +95,10 @@ class GpuExecutor:
             torch.cuda.current_device()).multi_processor_count
 
     #: columns per compute unit up to which the classes of an admission share
-    #: a launch (the library's own line for spreading the columns of its
-    #: shorter frames over workgroups)
+    #: a launch: above 512 rows, whose columns the library always spreads over
+    #: workgroups, and below, the lowest of its lines for that
     SHORT = 9
+    SHORT_LOW = 6
 
     def layout_for(self, k: int):
         return self.layout.get(k, (1, 0, 0))
@@ -139,7 +140,7 @@ class GpuExecutor:
         """The launches of an admission: (height class, its requests), tallest
         class first.  A class joins the launch of the next taller one while
         both leave their layout to the library and the columns together are at
-        most SHORT per compute unit: a launch that short spreads each column
+        most SHORT (SHORT_LOW up to 512 rows) per compute unit: a launch that short spreads each column
         over a workgroup whatever its height, and two such launches in a row
         leave the chip partly idle twice (two frames 1024x440 and one 1280x720:
         80 and 103 us one after the other).  That holds for costs on the grid:
@@ -159,9 +160,10 @@ class GpuExecutor:
                 hmax, dmax, cols = self.classes[top]
                 both = members + groups[k]
                 ncols = sum(self.cameras[r.camera].ncols() for r in both)
+                short = self.SHORT if hmax > 512 else self.SHORT_LOW
                 if (self.layout_for(top) == self.layout_for(k) == (1, 0, 0) and on_grid(both)
                         and len(both) <= self.max_frames
-                        and ncols <= min(self.SHORT * self.num_cu, self.max_frames * cols)
+                        and ncols <= min(short * self.num_cu, self.max_frames * cols)
                         and max(self.cameras[r.camera].handle.D for r in groups[k]) <= dmax):
                     launches[-1] = (top, both)
                     continue

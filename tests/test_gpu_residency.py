@@ -73,3 +73,31 @@ def test_frames_on_both_sides_of_the_line(H):
         torch.cuda.synchronize()
         assert_tiles_equal(out, ref, f"{label} {H}")
     h.close()
+
+
+@pytest.mark.parametrize("H,D,per_cu", [
+    (64, 64, 9), (65, 64, 6), (128, 128, 6), (320, 128, 6), (128, 256, 7), (320, 256, 7),
+    (321, 64, 7), (384, 128, 7), (384, 256, 9), (385, 64, 10), (448, 128, 10), (448, 256, 18),
+    (449, 64, 18), (512, 128, 18), (512, 256, 28),
+])
+def test_line_between_spread_and_one_wave(H, D, per_cu):
+    """An automatic batch spreads its columns up to so many per compute unit."""
+    import torch
+    announce(f"line of automatic batches, H={H} D={D}")
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    p, disp = frame_and_params(H, D, "columns", s=1, cols=TILE)
+    ref = oracle.frame(p, disp[:, :TILE])
+    cols = per_cu * cus + 1
+    h = P.Stixels(dict(p, max_width=cols, flags=1))
+    frame = to_device(disp[:, :TILE]).repeat(1, -(-cols // TILE))
+    b = P.Batch(1, cols, H, D)
+    for n, spread in ((cols - 1, True), (cols, False)):
+        o = P.FrameOutput(n, H, device())
+        b.compute([(h, frame[:, :n].contiguous(), o)])
+        torch.cuda.synchronize()
+        assert (b.waves() > 1) == spread
+        host = o.to_host()
+        for i in range(0, n // TILE * TILE, 8 * TILE):
+            assert_frames_equal({k: v[i:i + TILE] for k, v in host.items()}, ref, f"{n} from {i}")
+    b.close()
+    h.close()

@@ -46,6 +46,12 @@ def test_columns_per_compute_unit(num_cu, want):
     assert groups(executor(CAMERAS, num_cu=num_cu), [0, 1, 0]) == want
 
 
+@pytest.mark.parametrize("num_cu,want", [(56, [(MID, [0, 2])]), (55, [(MID, [0]), (LOW, [2])])])
+def test_columns_per_compute_unit_below_513_rows(num_cu, want):
+    # 204 + 128 = 332 columns: 6 of each of 56 compute units hold them
+    assert groups(executor(CAMERAS, num_cu=num_cu), [0, 2]) == want
+
+
 def test_limits_of_the_taller_class():
     # the taller class's batch holds max_frames frames of its own column count
     narrow = [(1024, 440, 128), (300, 720, 128)]
