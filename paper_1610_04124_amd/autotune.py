@@ -119,6 +119,7 @@ def tune(batch, items, stream, replays: int = 9, cache_path: str | None = DEFAUL
     layouts = [(w, 1) for w in waves] + ([(1, 2)] if 1 in waves else [])
     timings = {}
     ntasks = {}
+    held = {}                                      # waves a column really has
     for w, c in layouts:
         batch.set_waves(w)
         batch.set_columns(c)
@@ -132,6 +133,7 @@ def tune(batch, items, stream, replays: int = 9, cache_path: str | None = DEFAUL
             batch.capture(items, stream)
             timings[(c, w, g)] = _time(lambda: batch.replay(stream), stream, replays)
             ntasks[(c, w, g)] = nt
+            held[(c, w, g)] = batch.waves()
     # Candidates within 1.5 % of the fastest are timed again, in three
     # interleaved blocks of `replays` replays each (so that a drift of the
     # clock or of the memory system over the sweep does not pick for them),
@@ -151,12 +153,14 @@ def tune(batch, items, stream, replays: int = 9, cache_path: str | None = DEFAUL
         for k in close:
             timings[k] = statistics.median(samples[k])
     # near-ties (within 0.25 %, about the replay-to-replay noise) go to one
-    # column per wave, fewer waves per column, then fewer workgroups: the
-    # same speed for less of the device.  (A 1 % margin picked grids that
+    # column per wave, fewer waves per column (those it has: the automatic
+    # setting, 0, spreads it over several), then fewer workgroups: the same
+    # speed for less of the device.  (A 1 % margin picked grids that
     # the kernel trace then showed 2-3 % slower.)
     fastest = min(timings[k] for k in close) if len(close) > 1 else fastest
     timings = {k: v for k, v in timings.items() if len(close) <= 1 or k in close}
-    best = min((k for k, v in timings.items() if v <= fastest * 1.0025), key=lambda k: k)
+    best = min((k for k, v in timings.items() if v <= fastest * 1.0025),
+               key=lambda k: (k[0], held[k], k[2]))
     batch.set_columns(best[0])
     batch.set_waves(best[1])
     batch.set_workgroups(best[2])

@@ -126,3 +126,29 @@ def test_cache_applies_the_stored_choice_without_timing(timed, tmp_path):
     rec2 = autotune.tune(b2, items(), None, replays=3, cache_path=path, waves=(1,))
     assert rec2["cached"] and rec2["workgroups"] == 3072
     assert b2.captured == (1, 1, 3072) and len(timed["calls"]) == n
+
+
+class SpreadBatch(FakeBatch):
+    """Waves 0 (automatic) gives `spread` waves to a column."""
+
+    def __init__(self, spread, gmax, ntasks):
+        super().__init__(gmax, ntasks)
+        self.spread = spread
+
+    def waves(self):
+        return self.w or self.spread
+
+
+def test_near_ties_count_the_waves_a_column_really_has(timed):
+    # automatic: eight waves a column, 0.1 % faster than one wave
+    b = SpreadBatch(8, {0: 512, 1: 4096}, 13056)
+    timed["first"] = {(1, 0, 512): 1.000, (1, 1, 4096): 1.001}
+    timed["later"] = {(1, 0, 512): 1.000, (1, 1, 4096): 1.001}
+    rec = autotune.tune(b, items(), None, replays=3, cache_path=None, waves=(0, 1))
+    assert (rec["waves"], rec["workgroups"]) == (1, 4096)
+    # 0.5 % is no tie
+    b = SpreadBatch(8, {0: 512, 1: 4096}, 13056)
+    timed["seen"].clear()
+    timed["first"][(1, 1, 4096)] = timed["later"][(1, 1, 4096)] = 1.005
+    rec = autotune.tune(b, items(), None, replays=3, cache_path=None, waves=(0, 1))
+    assert (rec["waves"], rec["workgroups"]) == (0, 512)
