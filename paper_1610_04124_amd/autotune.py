@@ -125,8 +125,10 @@ def tune(batch, items, stream, replays: int = 9, cache_path: str | None = DEFAUL
         batch.set_columns(c)
         batch.set_workgroups(0)
         batch.capture(items, stream)
-        if batch.columns() != c or (batch.waves() != w if w else batch.waves() <= max(WAVES)):
-            continue                               # not available for these rows
+        # not available for these rows, or automatic and not spread: one wave
+        # (a spread column has at least four)
+        if batch.columns() != c or (batch.waves() != w if w else batch.waves() == 1):
+            continue
         gmax, nt = batch.info()
         for g in candidates(gmax, nt):
             batch.set_workgroups(g)

@@ -152,3 +152,14 @@ def test_near_ties_count_the_waves_a_column_really_has(timed):
     timed["first"][(1, 1, 4096)] = timed["later"][(1, 1, 4096)] = 1.005
     rec = autotune.tune(b, items(), None, replays=3, cache_path=None, waves=(0, 1))
     assert (rec["waves"], rec["workgroups"]) == (0, 512)
+
+
+@pytest.mark.parametrize("spread,tried", [(4, True), (8, True), (16, True), (1, False)])
+def test_automatic_layout_is_timed_where_it_spreads_a_column(timed, spread, tried):
+    """Columns of up to 64 rows are spread over four waves, as many as can be
+    asked for; only one wave means that the automatic setting is not spread."""
+    b = SpreadBatch(spread, {0: 512, 1: 4096, 4: 1024}, 13056)
+    timed["first"] = {(1, 0, 512): 0.5}
+    rec = autotune.tune(b, items(), None, replays=3, cache_path=None, waves=(0, 1, 4))
+    assert any(k.startswith("w0/") for k in rec["tried"]) == tried
+    assert (rec["waves"] == 0) == tried
