@@ -10,8 +10,8 @@ persistent kernel: more hide more latency; fewer leave each SIMD less
 contended and shorten the tail when the column tasks do not divide evenly
 into the resident set.  For a job list the tuner captures the launch once
 per candidate, times a few graph replays with HIP events, keeps the fastest,
-and caches the choice on disk keyed by the device and the job signature
-(the multiset of frame height, width, stixel width and d_range).
+and caches the choice on disk keyed by the device, the built library and the
+job signature (the multiset of frame height, width, stixel width and d_range).
 
 Per-frame path: waves per column and the placement of the object prefix
 table (global memory, or an LDS copy per column where it fits), timed the
@@ -22,9 +22,12 @@ Results never depend on the choices: every candidate computes the same bits.
 
 from __future__ import annotations
 
+import hashlib
 import json
 import os
 import statistics
+
+from . import binding
 
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "stixels_autotune.json")
 
@@ -42,6 +45,16 @@ def device_key() -> str:
     import torch
     p = torch.cuda.get_device_properties(torch.cuda.current_device())
     return f"{p.name}|{getattr(p, 'gcnArchName', '')}|cu{p.multi_processor_count}"
+
+
+def library_key() -> str:
+    """Identity of the built library: which layout is fastest changes with its
+    kernels."""
+    try:
+        with open(binding.lib_path(), "rb") as f:
+            return hashlib.sha256(f.read()).hexdigest()[:16]
+    except OSError:
+        return "none"
 
 
 def _load(path):
@@ -104,8 +117,10 @@ def tune(batch, items, stream, replays: int = 9, cache_path: str | None = DEFAUL
     with the chosen configuration.  waves 0 stands for the automatic choice
     where that spreads a column over a workgroup (elsewhere it equals one of
     the others and is not timed)."""
-    key = device_key() + "||" + signature(items)
-    cache = _load(cache_path) if cache_path else {}
+    cache, key = {}, None
+    if cache_path:
+        cache = _load(cache_path)
+        key = f"{device_key()}|{library_key()}||{signature(items)}"
     if not force and key in cache and "columns" in cache[key]:
         rec = cache[key]
         batch.set_columns(rec["columns"])

@@ -119,11 +119,16 @@ def to_pose(pose) -> Pose:
 _lib = None
 
 
+def lib_path() -> str:
+    """The library that this process loads."""
+    return PHASES_LIB_PATH if os.environ.get("STIXELS_PHASE_TIMING") == "1" else LIB_PATH
+
+
 def lib():
     """Load the in-tree HIP library; raise if it has not been built."""
     global _lib
     if _lib is None:
-        path = PHASES_LIB_PATH if os.environ.get("STIXELS_PHASE_TIMING") == "1" else LIB_PATH
+        path = lib_path()
         if not os.path.exists(path):
             raise ImportError(f"{path} is missing: build it with "
                               "`python -m paper_1610_04124_amd.build` (no CPU fallback exists)")

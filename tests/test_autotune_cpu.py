@@ -163,3 +163,37 @@ def test_automatic_layout_is_timed_where_it_spreads_a_column(timed, spread, trie
     rec = autotune.tune(b, items(), None, replays=3, cache_path=None, waves=(0, 1, 4))
     assert any(k.startswith("w0/") for k in rec["tried"]) == tried
     assert (rec["waves"] == 0) == tried
+
+
+def test_cache_of_another_library_is_not_applied(timed, tmp_path, monkeypatch):
+    path = str(tmp_path / "tune.json")
+    monkeypatch.setattr(autotune, "library_key", lambda: "old", raising=False)
+    timed["first"] = {(1, 1, 3072): 0.9}
+    rec = autotune.tune(FakeBatch({1: 4096}, 13056), items(), None, replays=3, cache_path=path,
+                        waves=(1,))
+    assert rec["workgroups"] == 3072
+    # another build: timed anew, and either's record applies to its own library
+    monkeypatch.setattr(autotune, "library_key", lambda: "new", raising=False)
+    timed["seen"].clear()
+    timed["first"] = {(1, 1, 4096): 0.9}
+    b = FakeBatch({1: 4096}, 13056)
+    rec = autotune.tune(b, items(), None, replays=3, cache_path=path, waves=(1,))
+    assert not rec["cached"] and rec["workgroups"] == 4096
+    for lib, g in (("old", 3072), ("new", 4096)):
+        monkeypatch.setattr(autotune, "library_key", lambda: lib, raising=False)
+        rec = autotune.tune(FakeBatch({1: 4096}, 13056), items(), None, replays=3, cache_path=path,
+                            waves=(1,))
+        assert rec["cached"] and rec["workgroups"] == g
+
+
+def test_library_key_follows_the_built_file(tmp_path, monkeypatch):
+    from paper_1610_04124_amd import binding
+    a, b = tmp_path / "a.so", tmp_path / "b.so"
+    a.write_bytes(b"one")
+    b.write_bytes(b"two")
+    keys = []
+    for path in (a, b, a):
+        monkeypatch.setattr(binding, "LIB_PATH", str(path))
+        monkeypatch.setenv("STIXELS_PHASE_TIMING", "0")
+        keys.append(autotune.library_key())
+    assert keys[0] == keys[2] != keys[1]
