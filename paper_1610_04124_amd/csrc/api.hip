@@ -242,7 +242,7 @@ thread_local std::string g_create_error;
 
 // Bytes of the object prefix tables' entries 32 i for the widest frame.
 size_t edge_bytes(const stixels_handle* h) {
-    return (size_t)h->ncols_max * h->D * kEdgeFloats * sizeof(float);
+    return (size_t)h->ncols_max * h->D * edge_row_floats(h->Hmax) * sizeof(float);
 }
 
 // Path of stixels_compute: the request, or automatically the staged kernels.

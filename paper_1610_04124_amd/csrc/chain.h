@@ -92,8 +92,8 @@ struct ChainFlags {
 // rows keep 0.21 of the far groups of a road scene instead of 0.27, for four
 // times the bounds.)
 constexpr int kBlock = 32;
-constexpr int kBoundStride = kEdgeFloats;               // block boundaries
-static_assert(kMaxHeight / kBlock + 1 == kEdgeFloats, "entries 32 i of the table");
+constexpr int kBoundStride = kMaxHeight / kBlock + 1;   // block boundaries
+static_assert(edge_row_floats(kBlock) == 2, "entries 32 i of the table");
 
 // LDS of one column, laid out by its height (bytes; every part 16-aligned):
 // per base b {PA, PN2, diving, gravity threshold} and {PG, PS, PM, unused}; per
@@ -278,20 +278,20 @@ __device__ __forceinline__ float* chain_edges(const ChainLds& L) {
     return reinterpret_cast<float*>(L.ring);
 }
 
-// Stages them from the table of entries 32 i (rows of kEdgeFloats).
+// Stages them from the table of entries 32 i (rows of edge_row_floats(H)).
 __device__ __forceinline__ void chain_load_edges(const ChainCol& c, const ChainLds& L,
                                                  const float* edge, const int wave, const int nw) {
     const int lane = threadIdx.x & 63;
-    const int nb = c.H / kBlock, nq = chain_edge_quads(c.H);
+    const int nb = c.H / kBlock, nq = chain_edge_quads(c.H), row = edge_row_floats(c.H);
     float* const tile = chain_edges(L);
-    const auto er = make_rsrc(edge, (uint32_t)(c.nrow * kEdgeFloats) * 4u);
+    const auto er = make_rsrc(edge, (uint32_t)(c.nrow * row) * 4u);
     const uint32_t off = (uint32_t)min(lane, nb) * 4u;
     constexpr int U = 8;
     for (int f0 = wave; f0 < c.nrow; f0 += U * nw) {
         float x[U];
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            x[u] = buf_load_b(er, off, (uint32_t)(min(f0 + u * nw, c.nrow - 1) * kEdgeFloats) * 4u);
+            x[u] = buf_load_b(er, off, (uint32_t)(min(f0 + u * nw, c.nrow - 1) * row) * 4u);
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (lane < 4 * nq && f0 + u * nw < c.nrow) tile[(f0 + u * nw) * 4 * nq + lane] = x[u];

@@ -57,7 +57,7 @@ struct ColumnIn {
     const float* rtab = nullptr;
     const int16_t* q;       // [H] reduced disparities of the column (LDS), -1 invalid
     const float* O_df;      // [D][D] object cost, row d (pixel disparity), column f (mean)
-    const float* PO_edge = nullptr; // PO at every 32nd entry, [rows][33] (chain.h)
+    const float* PO_edge = nullptr; // PO at every 32nd entry, [rows][H / 32 + 1] (chain.h)
     const float* PM = nullptr;      // [H+1] prefix of each pixel's smallest object cost (chain.h)
     int D;
     const int32_t* fg_hi;   // diving threshold per top-down image row

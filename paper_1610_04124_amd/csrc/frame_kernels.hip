@@ -183,10 +183,11 @@ __global__ __launch_bounds__(512) void tables_kernel(TablesArgs a) {
     // every line of it).
     const int pstride = po_row_floats(H);
     float* PO = a.po + (size_t)col * D * pstride;
-    float* edge = a.edge + (size_t)col * D * kEdgeFloats;
+    const int erow = edge_row_floats(H);
+    float* edge = a.edge + (size_t)col * D * erow;
     const auto otr = make_rsrc(a.object_t, (uint32_t)(D * D) * 4u);
     const auto pow_ = make_rsrc(PO, (uint32_t)(fmax - fmin + 1) * (uint32_t)pstride * 4u);
-    const auto edr = make_rsrc(edge, (uint32_t)(fmax - fmin + 1) * (uint32_t)kEdgeFloats * 4u);
+    const auto edr = make_rsrc(edge, (uint32_t)(fmax - fmin + 1) * (uint32_t)erow * 4u);
     constexpr int NC = 4;                        // 64-bin chunks of a cost row (<= 256 bins)
     const int nch = (D + 63) >> 6;
     float* const stg = ostg[wave];
@@ -225,7 +226,7 @@ __global__ __launch_bounds__(512) void tables_kernel(TablesArgs a) {
         }
         if (f + 8 <= f1) load_row(f + 8);
         const uint32_t rowoff = (uint32_t)(f - f0) * (uint32_t)pstride * 4u;
-        const uint32_t edgeoff = (uint32_t)(f - f0) * (uint32_t)kEdgeFloats * 4u;
+        const uint32_t edgeoff = (uint32_t)(f - f0) * (uint32_t)erow * 4u;
         if (lane == 0) {
             buf_store_b(pow_, 0.0f, 12u, rowoff);
             buf_store_b(edr, 0.0f, 0u, edgeoff);
@@ -265,7 +266,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void chain_kernel(DpArgs a) {
     const int pstride = po_row_floats(a.H);
     in.PO = a.po + (size_t)col * a.D * pstride + 3;
     in.po_stride = pstride;
-    in.PO_edge = a.edge + (size_t)col * a.D * kEdgeFloats;
+    in.PO_edge = a.edge + (size_t)col * a.D * edge_row_floats(a.H);
     in.fbase = __builtin_amdgcn_readfirstlane(a.range[2 * col]);
     in.fmax = __builtin_amdgcn_readfirstlane(a.range[2 * col + 1]);
     in.PM = a.prefix + ((size_t)4 * a.ncols + col) * stride;

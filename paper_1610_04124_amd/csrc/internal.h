@@ -10,7 +10,8 @@
 //   PO     float [ncols][D][po_row_floats(h)]  object prefix table, row f-fmin
 //                                      holds sums over rows of O[q_v][f]; entry
 //                                      i sits at float i + 3 of its row
-//   edge   float [ncols][D][33]        entries 32 i of the rows of PO
+//   edge   float [ncols][D][h / 32 + 1]  entries 32 i of the rows of PO (with online
+//                                      object costs and for stage times only)
 // Every cost value is a multiple of 2^-g and every partial sum stays below
 // 2^(24-g) in magnitude (checked when a handle is created), so FP32 adds,
 // subtractions and minima are exact and their order does not matter.
@@ -39,7 +40,7 @@ constexpr size_t kTableGuardBytes = 64 * 1024;
 // first at float 3: entries 4l+1 .. 4l+4 form one aligned 16-byte store) and
 // of a row of its entries 32 i.
 __host__ __device__ constexpr int po_row_floats(int h) { return ((h + 10) / 4) * 4; }
-constexpr int kEdgeFloats = kMaxHeight / 32 + 1;
+__host__ __device__ constexpr int edge_row_floats(int h) { return h / 32 + 1; }
 
 // Instantiated slot counts of the recurrence kernels (64-row slots per lane);
 // a column runs on the smallest one that covers its height.

@@ -38,7 +38,7 @@ struct FrameWorkspace {
     float* prefix;     // [5][ncols][H+1]
     int32_t* range;    // [ncols][2]
     float* po;         // [ncols][D][po_row_floats(H)]
-    float* edge;       // [ncols][D][33]: entries 32 i of the rows of po
+    float* edge;       // [ncols][D][H / 32 + 1]: entries 32 i of the rows of po
 };
 
 struct FrameOutput {

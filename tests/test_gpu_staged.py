@@ -113,3 +113,22 @@ def test_spread_recurrence_over_tables_workgroup_sizes(cols):
     choose(h, "online costs")
     assert_frames_equal(gpu_frame(h, disp), oracle.frame(p, disp), f"{cols} columns")
     h.close()
+
+
+@pytest.mark.parametrize("H,D", [(1, 256), (16, 256), (31, 64), (64, 128), (440, 128), (1024, 256)])
+def test_table_edges_follow_the_rows(H, D):
+    """A handle's bytes per column: besides the object prefix table's space (a
+    padded row per bin, or the fused path's banded slot if that is larger), the
+    reduced pixels and five small tables, an entry per bin and 32 rows."""
+    announce(f"device bytes H={H} D={D}")
+    sizes = []
+    for cols in (100, 200):
+        h = P.Stixels(synth.make_params(stixel_width=1, max_disparity=D, max_width=cols,
+                                        max_height=H))
+        sizes.append(h.device_bytes())
+        h.close()
+    row = (H + 10) // 4 * 4
+    slot = (4 * (H + 1) + 3) // 4 * 4 + max(D * row, 64 * ((H + 63) // 64) * (D + 1))
+    table = max(4 * D * row, 4 * slot + 16)
+    edges = 4 * D * (H // 32 + 1)
+    assert (sizes[1] - sizes[0]) / 100 <= table + 2 * H + 20 * (H + 1) + 8 + edges + 16
