@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes as C
 import math
+import operator
 import os
 
 import numpy as np
@@ -244,7 +245,9 @@ class FrameOutput:
 
     def __init__(self, ncols: int, capacity: int, device):
         import torch
-        self.ncols, self.capacity = int(ncols), int(capacity)
+        self.ncols, self.capacity = operator.index(ncols), operator.index(capacity)
+        if self.ncols < 0 or self.capacity < 0:
+            raise RuntimeError(f"FrameOutput of {self.ncols} columns and capacity {self.capacity}")
         # one allocation and one zero fill for the four of them, each at a
         # multiple of 256 bytes
         sizes = [12 * self.ncols * self.capacity, 4 * self.ncols, 4 * self.ncols, self.ncols]
