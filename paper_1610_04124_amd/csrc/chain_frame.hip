@@ -217,7 +217,8 @@ __attribute__((amdgpu_waves_per_eu(4))) void chain_frame_kernel(const ChainArgs)
     const Const<ChainArgs> a = (Const<ChainArgs>)__builtin_amdgcn_kernarg_segment_ptr();
     const int tid = threadIdx.x, lane = tid & 63, nt = (int)blockDim.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = nt >> 6;
-    unsigned int own = 0, own4 = 0;              // kArena: this workgroup's table space
+    unsigned int own = 0, own4 = 0;              // kArena: this workgroup's table space,
+    bool full = false;                           // and whether it was refused more
 #ifdef STX_PHASE_TIMING
     // wave 0 stamps the shader clock at each phase boundary of a batch's column
     const unsigned long long t_entry = __builtin_amdgcn_s_memtime();
@@ -319,25 +320,20 @@ __attribute__((amdgpu_waves_per_eu(4))) void chain_frame_kernel(const ChainArgs)
             if (own4 < need4) {
                 if (tid == 0) {
                     const Const<ChainArgs> A = again(a);
-                    unsigned int* const used4 = &A->head->used4;
-                    place = arena_take(
-                        A->room4, need4,
-                        [&]() {
-                            return __hip_atomic_load(used4, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT);
-                        },
-                        [&](unsigned int n) { return atomicAdd(used4, n); });
+                    place = arena_take(A->room4, need4, full, [&](unsigned int n) {
+                        return atomicAdd(&A->head->used4, n);
+                    });
                     if (place == kNoPlace) A->rest[atomicAdd(&A->head->nrest, 1u)] = col;
                 }
                 __syncthreads();
                 const unsigned int at = (unsigned int)__builtin_amdgcn_readfirstlane((int)place);
-                const bool left = at == kNoPlace;
-                if (!left) {
+                full = at == kNoPlace;
+                if (!full) {
                     own = at;
                     own4 = need4;
                 }
                 __syncthreads();                 // before the next column writes place
-                if (left) continue;
+                if (full) continue;
             }
             po = again(a)->po + (size_t)own * 4;
         } else {

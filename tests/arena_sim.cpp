@@ -11,6 +11,7 @@ int main(int argc, char** argv) {
     const unsigned int need = (unsigned)strtoul(argv[2], nullptr, 10);
     const long columns = atol(argv[3]);
     static unsigned int own[1024];
+    static bool full[1024];
     for (unsigned int& o : own) o = stx::persist::kNoPlace;
     unsigned int used = 0;
     long given = 0, bad = 0;
@@ -18,9 +19,10 @@ int main(int argc, char** argv) {
         unsigned int& mine = own[c % 1024];
         if (mine != stx::persist::kNoPlace) continue;
         const unsigned int at = stx::persist::arena_take(
-            room, need, [&] { return used; },
+            room, need, full[c % 1024],
             [&](unsigned int n) { const unsigned int was = used; used += n; return was; });
-        if (at == stx::persist::kNoPlace) continue;
+        full[c % 1024] = at == stx::persist::kNoPlace;
+        if (full[c % 1024]) continue;
         ++given;
         bad += at > room || need > room - at;
         for (const unsigned int o : own)
