@@ -10,7 +10,6 @@ from __future__ import annotations
 
 import ctypes as C
 import math
-import operator
 import os
 
 import numpy as np
@@ -245,12 +244,13 @@ class FrameOutput:
 
     def __init__(self, ncols: int, capacity: int, device):
         import torch
-        self.ncols, self.capacity = operator.index(ncols), operator.index(capacity)
-        if self.ncols < 0 or self.capacity < 0:
-            raise RuntimeError(f"FrameOutput of {self.ncols} columns and capacity {self.capacity}")
+        if ncols < 0 or capacity < 0:
+            raise RuntimeError(f"FrameOutput of {ncols} columns and capacity {capacity}")
+        self.ncols, self.capacity = int(ncols), int(capacity)
         # one allocation and one zero fill for the four of them, each at a
-        # multiple of 256 bytes
-        sizes = [12 * self.ncols * self.capacity, 4 * self.ncols, 4 * self.ncols, self.ncols]
+        # multiple of 256 bytes (sizes that are no whole numbers raise TypeError
+        # at the rounding)
+        sizes = [12 * ncols * capacity, 4 * ncols, 4 * ncols, ncols]
         at, end = [], 0
         for n in sizes:
             at.append(end)

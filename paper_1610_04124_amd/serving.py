@@ -147,12 +147,13 @@ class GpuExecutor:
         one frame with costs off it sends its whole launch to the one-wave
         kernel with stored links, sized for the tallest frame, so classes join
         only if every frame of both is on the grid."""
-        def on_grid(rs):
-            return all(getattr(self.cameras[r.camera].handle, "on_grid", True) for r in rs)
-
-        groups = {}
+        groups, off_grid = {}, set()
         for r in reqs:
-            groups.setdefault(self.cameras[r.camera].height_class(), []).append(r)
+            c = self.cameras[r.camera]
+            k = c.height_class()
+            groups.setdefault(k, []).append(r)
+            if not getattr(c.handle, "on_grid", True):
+                off_grid.add(k)
         launches = []
         for k in sorted(groups, reverse=True):
             if launches:
@@ -161,7 +162,8 @@ class GpuExecutor:
                 both = members + groups[k]
                 ncols = sum(self.cameras[r.camera].ncols() for r in both)
                 short = self.SHORT if hmax > 512 else self.SHORT_LOW
-                if (self.layout_for(top) == self.layout_for(k) == (1, 0, 0) and on_grid(both)
+                if (self.layout_for(top) == self.layout_for(k) == (1, 0, 0)
+                        and top not in off_grid and k not in off_grid
                         and len(both) <= self.max_frames
                         and ncols <= min(short * self.num_cu, self.max_frames * cols)
                         and max(self.cameras[r.camera].handle.D for r in groups[k]) <= dmax):
