@@ -4,8 +4,8 @@ One step = the whole hot path (column reduction, prefix tables, the
 three-class recurrence and backtracking) over one batch of 64 synthetic
 1024x440 frames (seeds 0..63), inputs resident in HBM.  The timed path is the
 persistent batched launch replayed from a HIP graph.  Beside it: the plain
-per-frame path (three staged kernels, and one fused launch) with per-frame
-latency percentiles and the HBM fraction of its reduction and table kernels;
+per-frame path (staged and fused, by default one launch each) with per-frame
+latency percentiles, and the times of its stages as kernels of their own;
 the 2048x880 batches; the 256-frame uneven batch; 64 stereo pairs through
 the semi-global matching stage and on into stixels; serving of 8 camera
 streams for 60 s; the CPU oracle on the host cores.
@@ -392,11 +392,12 @@ def stereo(warmup, steps, tune_launch=True):
 
 
 def per_frame_legs(h, d_frames, outs, stream, steps, latency_frames, tune_launch):
-    """The per-frame paths: three staged kernels and one fused launch.  Per
-    path: throughput with frames back to back, and latency per frame (HIP
-    events around each call, a synchronisation between frames).  For the
-    staged path also the time of each kernel and the HBM fraction of the
-    reduction and table kernels."""
+    """The per-frame paths, staged and fused.  Per path: throughput with frames
+    back to back, and latency per frame (HIP events around each call, a
+    synchronisation between frames).  Also the stages as kernels of their own
+    (the staged path's form with waves or placement set, or with online object
+    costs; otherwise it is one launch): the time of each, and the HBM fraction
+    of the reduction and table kernels."""
     import torch
 
     from paper_1610_04124_amd import binding as B
@@ -434,7 +435,7 @@ def per_frame_legs(h, d_frames, outs, stream, steps, latency_frames, tune_launch
     if frame_tuned is not None:
         res["po_placement"] = "lds" if frame_tuned["po_placement"] == 2 else "hbm"
         res["autotune_tried_ms"] = frame_tuned["tried"]
-    # stage split: kernel times between HIP events, median over frames
+    # stage split, as kernels of their own: times between HIP events, median over frames
     times = [h.stage_times(d_frames[i % len(d_frames)], outs[i % len(d_frames)], stream)
              for i in range(32)]
     med = [statistics.median(t[k] for t in times) for k in range(3)]
@@ -536,7 +537,7 @@ def profile_mode(args):
             width 5), replayed from a HIP graph --launches times;
     hires   the same over 16 frames of 2048x880 (stixel width 5, d_range 256);
     uneven  the 256-frame uneven batch;
-    frame   the staged per-frame path (three kernels) on the 64 frames;
+    frame   the staged per-frame path on the 64 frames;
     fused   the fused per-frame path (one launch per frame) on the 64 frames;
     sgm     the semi-global matching stage over 64 stereo pairs 1024x440;
     copy    a plain 256 MiB device-to-device copy, whose FETCH_SIZE and

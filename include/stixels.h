@@ -124,8 +124,10 @@ typedef struct {
     int32_t *counts;             /* [ncols] */
     stixels_record *records;     /* [ncols][capacity], bottom-up within a column */
     float *total_cost;           /* [ncols], min(OB^{h-1}, GR^{h-1}, SK^{h-1}) */
-    uint8_t *overflow;           /* [ncols]; 1 = truncated to capacity, 255 = backtracking
-                                    found no predecessor (never expected; counts is 0) */
+    uint8_t *overflow;           /* [ncols]; 1 = truncated to capacity, 255 = the column was
+                                    given up (never expected; counts is 0): backtracking
+                                    found no predecessor, or, where a column is spread over
+                                    a workgroup, a wave waited past its limit for another */
     int32_t capacity;
     int32_t reserved0;
 } stixels_output;
@@ -150,7 +152,9 @@ typedef struct {
 /* Validate the parameters, build the offline cost tables of Sec. 3.4 on the
  * host in FP64 (Eq. 4 for every pair of pixel disparity and model disparity,
  * rounded to the 2^-g grid), upload them and allocate a workspace for frames
- * up to max_width x max_height.  Must be called with the target device
+ * up to max_width x max_height (mostly the columns' object prefix tables; of the
+ * whole, some 4 % are tables that only online object costs and
+ * stixels_debug_stage_times use; stixels_device_bytes says how much).  Must be called with the target device
  * current.  Returns STIXELS_E_RANGE when (max_height + 1) * (largest table
  * cost) plus the priors could leave the exact range of FP32 on the grid, or
  * when max_height * max_disparity > 2^20. */
@@ -435,8 +439,10 @@ enum { STIXELS_STAGE_REDUCED = 0, STIXELS_STAGE_PREFIX = 1, STIXELS_STAGE_RANGE 
 int stixels_debug_stage(const stixels_handle *h, int32_t which, void *host_dst, size_t bytes,
                         void *stream);
 
-/* One frame through the staged path of stixels_compute with HIP events on
- * `stream` between its three kernels; synchronises and writes the
+/* One frame through the staged path as three kernels, with HIP events on
+ * `stream` between them (with neither waves nor placement set stixels_compute
+ * itself runs them as one launch, which takes less than their sum; the last
+ * kernel is then the recurrence spread over workgroups); synchronises and writes the
  * milliseconds of the reduction (Sec. 4.1), the prefix tables (Sec. 4.2) and
  * the recurrence with backtracking (Sec. 4.3-4.4) to host_ms[0..2].  For
  * measurements; the results equal those of stixels_compute. */
@@ -479,8 +485,12 @@ typedef struct {
 } stixels_sgm_params;
 
 /* Validate, and allocate the workspace: both views' census words and the
- * summed costs, uint16 [max_frames][max_height][max_width][max_disparity]
- * (device bytes: stixels_sgm_device_bytes).  STIXELS_E_INVALID_ARG with the
+ * path costs.  With p2 <= 193 those are bytes, one plane of
+ * [max_frames][max_height][max_width][max_disparity] for each of three
+ * directions, or of four where the largest call has few rows per compute unit
+ * (17 for up to 64 disparities, 14 for 128, 8 for 256).  With larger penalties, and
+ * where the planes find no memory, they are sums, one plane of uint16 (device
+ * bytes: stixels_sgm_device_bytes).  STIXELS_E_INVALID_ARG with the
  * reason in stixels_sgm_last_error(NULL), or STIXELS_E_NOMEM. */
 int stixels_sgm_create(const stixels_sgm_params *params, stixels_sgm **out);
 int stixels_sgm_destroy(stixels_sgm *m);

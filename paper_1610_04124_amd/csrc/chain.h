@@ -97,8 +97,9 @@ static_assert(edge_row_floats(kBlock) == 2, "entries 32 i of the table");
 
 // LDS of one column, laid out by its height (bytes; every part 16-aligned):
 // per base b {PA, PN2, diving, gravity threshold} and {PG, PS, PM, unused}; per
-// row the published {C_o, f << 16 | b, C_g, C_s} (before that, in its first two
-// words, the far candidates' {cost, f << 16 | b}); the ring, {data, data +
+// row the published {C_o, f << 16 | b, C_g, C_s} (before that the far candidates'
+// {cost, f << 16 | b}: those of even base groups in its first two words, of odd
+// ones in the other two); the ring, {data, data +
 // ground prior, f << 16 | b, pixel's ground / sky cost} per step and lane; the
 // bounds; the groups' summaries; the flags.
 struct ChainLds {

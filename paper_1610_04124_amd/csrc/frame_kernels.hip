@@ -125,8 +125,8 @@ __global__ __launch_bounds__(512) void tables_kernel(TablesArgs a) {
     const int nu = (H + 255) >> 8;
     if (wave < 5) {
         // wave t scans small table t: ground, sky, 2q+1 and 2 over the valid
-        // pixels and their smallest object costs (five chains side by side rather than one after another),
-        // lane l taking the rows 256 u + 4 l .. 256 u + 4 l + 3, so that a
+        // pixels and their smallest object costs (five chains side by side
+        // rather than one after another), lane l taking the rows 256 u + 4 l .. 256 u + 4 l + 3, so that a
         // table of 440 rows is two loads and scans deep rather than seven
         const int t = __builtin_amdgcn_readfirstlane(wave);
         float* P = a.prefix + ((size_t)t * ncols + col) * stride;
