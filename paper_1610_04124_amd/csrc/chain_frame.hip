@@ -468,10 +468,11 @@ size_t chain_arena_bytes(int ncols, int H, int D, int tables) {
 }
 
 // A frame whose tables all fit is launched like any other, 1.1 to 9 times as
-// fast as a wave per column.  In a workspace that is shared a column costs a
-// fixed 40 us besides (its task, its place, 4 workgroups to a compute unit), and
-// of few rows and disparities a wave takes less.  Spread / a wave per column, us,
-// rows x bins, columns: 32x256 4,096 150 / 98; 64x128 4,096 166 / 119; 96x128
+// fast as a wave per column.  In a shared workspace the resident workgroups take
+// columns in turn, with a task and a place handed out and barriers around each
+// (64 rows and bins: 41 us a column, 21 in a launch with a workgroup each), and of
+// few rows and disparities a wave takes less.  Spread / a wave per column, us, rows
+// x bins, columns: 32x256 4,096 150 / 98; 64x128 4,096 166 / 119; 96x128
 // 2,048 128 / 126, 8,192 407 / 349; 128x64 8,192 424 / 271; 64x256 2,048 92 / 103,
 // 4,096 168 / 165, 8,192 368 / 290; 128x128 2,048 147 / 156, 4,096 257 / 249, 8,192
 // 532 / 440; 192x128 8,192 768 / 941; 96x256 8,192 459 / 670; 440x128 4,096 921 /

@@ -140,13 +140,14 @@ class GpuExecutor:
         """The launches of an admission: (height class, its requests), tallest
         class first.  A class joins the launch of the next taller one while
         both leave their layout to the library and the columns together are at
-        most SHORT (SHORT_LOW up to 512 rows) per compute unit: a launch that short spreads each column
-        over a workgroup whatever its height, and two such launches in a row
-        leave the chip partly idle twice (two frames 1024x440 and one 1280x720:
-        80 and 103 us one after the other).  That holds for costs on the grid:
-        one frame with costs off it sends its whole launch to the one-wave
-        kernel with stored links, sized for the tallest frame, so classes join
-        only if every frame of both is on the grid."""
+        most SHORT (SHORT_LOW up to 512 rows) per compute unit: a launch that
+        short spreads each column over a workgroup whatever its height, and two
+        such launches in a row leave the chip partly idle twice (two frames
+        1024x440 and one 1280x720: 80 and 103 us one after the other).  That
+        holds for costs on the grid: one frame with costs off it sends its
+        whole launch to the one-wave kernel with stored links, sized for the
+        tallest frame, so classes join only if every frame of both is on the
+        grid."""
         groups, off_grid = {}, set()
         for r in reqs:
             c = self.cameras[r.camera]
